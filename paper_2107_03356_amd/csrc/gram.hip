@@ -20,7 +20,10 @@
 // k_gram_blocks_reduce.
 // The fast static mode's k_gram_blocks32 runs the block Gram on fp32 MFMA in
 // 256 x 256 tiles (see there).
+#include <type_traits>
+
 #include "internal.h"
+#include "split_mfma.h"
 #include "tile_util.h"
 
 namespace mfac {
@@ -375,27 +378,24 @@ __global__ __launch_bounds__(256) void k_gram_blocks_reduce(const double* __rest
     }
 }
 
-// Static blocks on fp32 MFMA (v_mfma_f32_16x16x4f32), for the fast mode. At
-// twice the fp64 rate the 128 x 128 tiles of k_gram_blocks are bound by
-// their operand traffic out of L2, so this kernel takes 256 x 256 lower
-// tiles: one work-group of 16 waves per tile and column split, each wave
-// owning 64 x 64 as 4 x 4 MFMA tiles (two MFMAs per LDS read instead of
-// 1.33, half the operand bytes per flop), 32-column chunks double-buffered
-// in LDS (256 rows x 36 floats per operand: the 16-row x 4-k read of one
-// MFMA operand on distinct banks), the next chunk's loads in flight during
-// the MFMAs. Products accumulate in fp32 over at most SPLIT32 columns; wider
-// blocks are split and the splits summed in fp64 (k_gram_blocks_reduce).
-// In diagonal tiles the waves wholly above the diagonal only stage operands.
-constexpr int GT32 = 256;
-constexpr int KB32 = 32;
-constexpr int PITCH32 = KB32 + 4;
+// Static blocks of the fast mode: fp32 products on the bf16 matrix cores
+// (split_mfma.h), fp32 sums over at most SPLIT32 columns; wider blocks are split
+// and the splits summed in fp64 (k_gram_blocks_reduce). One work-group per
+// BM x BM lower tile and column split, waves of WM x WN, the columns in 16-wide
+// chunks double-buffered in LDS, converted as they are staged, the next chunk's
+// loads in flight during the MFMAs. 32 x 32 pieces wholly above the diagonal or
+// past row m are skipped, and the waves of a diagonal 256-tile are placed so
+// that the four SIMDs (waves go to them round-robin) hold 8, 8, 10 and 10 of its
+// 36 pieces.
 constexpr int SPLIT32 = 2048;
 
-__global__ __launch_bounds__(1024) void k_gram_blocks32(const float* __restrict__ G, int m, int64_t d, int B, int b0,
-                                                        int ntiles, int nsplit, int kcols, double mu,
-                                                        float* __restrict__ A, int mp, double* __restrict__ part) {
-    __shared__ float As[2][GT32][PITCH32];
-    __shared__ float Bs[2][GT32][PITCH32];
+template <int BM, int WM, int WN>
+__global__ __launch_bounds__((BM / WM) * (BM / WN) * 64, 2) void k_gram_blocks32(
+    const float* __restrict__ G, int m, int64_t d, int B, int b0, int ntiles, int nsplit, int kcols, double mu,
+    float* __restrict__ A, int mp, double* __restrict__ part) {
+    constexpr int NX = WM / 32, NY = WN / 32, NT = (BM / WM) * (BM / WN) * 64;
+    static_assert(NT == BM * 2, "two 4-value pieces per thread and operand");
+    __shared__ SplitChunk<BM> As[2], Bs[2];
     const int lid = xcd_remap(blockIdx.x, gridDim.x);
     const int per_block = ntiles * nsplit;
     const int bl = lid / per_block;
@@ -404,113 +404,123 @@ __global__ __launch_bounds__(1024) void k_gram_blocks32(const float* __restrict_
     const int tile = rem - sp * ntiles;
     int ti, tj;
     tile_of(tile, ti, tj);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // wave -> 64 x 64 piece (rows wr*64, columns wc*64): a permutation under
-    // which the ten pieces on or below the diagonal of a diagonal tile fall
-    // 3, 2, 3, 2 on the four SIMDs whether waves go round-robin (wave & 3) or
-    // in runs of four (wave >> 2), so such a tile costs three waves per SIMD
-    const int code = (int)((0xbfed76ca98354021ull >> (4 * wave)) & 15u);
-    const int wr = code >> 2, wc = code & 3;
-    const int rl = lane & 15, kl = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // wave -> piece (rows wr * WM, columns wc * WN)
+    int wr, wc;
+    if constexpr (BM == 256) {
+        // waves w and w + 4 share a SIMD: (1,0)+(0,2), (1,1)+(0,3), (0,0)+(0,1), (1,2)+(1,3)
+        const int code = (0x71326054 >> (4 * wave)) & 15;
+        wr = code >> 2;
+        wc = code & 3;
+    } else {
+        wr = wave / (BM / WN);
+        wc = wave % (BM / WN);
+    }
     const bool diag_tile = ti == tj;
-    const bool upper_wave = diag_tile && wr < wc;
     const int cbeg = sp * kcols;
     const int ncols = (B - cbeg) < kcols ? (B - cbeg) : kcols;
     const float* base = G + (int64_t)(b0 + bl) * B + cbeg;
-    const int ra0 = ti * GT32, rb0 = tj * GT32;
-    // staging: 256 rows x 32 columns per operand, 8 floats per thread and operand
-    const int sr = tid >> 2, sc = (tid & 3) * 8;
-    const bool oka = ra0 + sr < m, okb = rb0 + sr < m;
-    // loads from clamped, in-bounds addresses (ncols is a positive multiple of
-    // 4), the values outside the tile replaced by zeros in registers
-    const float* rowa = base + (int64_t)min(ra0 + sr, m - 1) * d;
-    const float* rowb = base + (int64_t)min(rb0 + sr, m - 1) * d;
-    float4 pa0, pa1, pb0, pb1;
-#define MFAC_G32_LOAD(K0_)                                                          \
-    {                                                                                    \
-        const int c_ = (K0_) + sc;                                                       \
-        const int ca_ = min(c_, ncols - 4), cb_ = min(c_ + 4, ncols - 4);                \
-        pa0 = *reinterpret_cast<const float4*>(rowa + ca_);                              \
-        pa1 = *reinterpret_cast<const float4*>(rowa + cb_);                              \
-        if (!diag_tile) {                                                                \
-            pb0 = *reinterpret_cast<const float4*>(rowb + ca_);                          \
-            pb1 = *reinterpret_cast<const float4*>(rowb + cb_);                          \
-        }                                                                                \
-    }
-#define MFAC_G32_STORE(BUF_, K0_)                                                   \
-    {                                                                                    \
-        const int c_ = (K0_) + sc;                                                       \
-        float4* a_ = reinterpret_cast<float4*>(&As[BUF_][sr][sc]);                       \
-        a_[0] = keep4(oka && c_ < ncols, pa0);                                           \
-        a_[1] = keep4(oka && c_ + 4 < ncols, pa1);                                       \
-        if (!diag_tile) {                                                                \
-            float4* b_ = reinterpret_cast<float4*>(&Bs[BUF_][sr][sc]);                   \
-            b_[0] = keep4(okb && c_ < ncols, pb0);                                       \
-            b_[1] = keep4(okb && c_ + 4 < ncols, pb1);                                   \
-        }                                                                                \
-    }
-
-    v4f acc[4][4];
+    const int ra0 = ti * BM, rb0 = tj * BM;
+    // this wave's 32 x 32 pieces that hold lower-triangle entries of rows below m
+    unsigned on = 0;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < NX; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y) acc[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
-    const int nchunk = (ncols + KB32 - 1) / KB32;
-    MFAC_G32_LOAD(0)
-    MFAC_G32_STORE(0, 0)
-    __syncthreads();
-    for (int c = 0; c < nchunk; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < nchunk) MFAC_G32_LOAD((c + 1) * KB32)
-        float (*Ab)[PITCH32] = As[buf];
-        float (*Bb)[PITCH32] = diag_tile ? As[buf] : Bs[buf];
-        if (!upper_wave) {
-#pragma unroll
-            for (int kk = 0; kk < KB32 / 4; ++kk) {
-                float av[4], bv[4];
-#pragma unroll
-                for (int x = 0; x < 4; ++x) av[x] = Ab[wr * 64 + x * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                for (int y = 0; y < 4; ++y) bv[y] = Bb[wc * 64 + y * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                for (int x = 0; x < 4; ++x)
-#pragma unroll
-                    for (int y = 0; y < 4; ++y)
-                        acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[x], bv[y], acc[x][y], 0, 0, 0);
-            }
+        for (int y = 0; y < NY; ++y) {
+            const int r = ra0 + wr * WM + 32 * x, c = rb0 + wc * WN + 32 * y;
+            if (r < m && c < m && r >= c) on |= 1u << (x * NY + y);
         }
-        if (c + 1 < nchunk) MFAC_G32_STORE(buf ^ 1, (c + 1) * KB32)
-        __syncthreads();
-    }
-#undef MFAC_G32_LOAD
-#undef MFAC_G32_STORE
-    if (upper_wave) return;
-    if (nsplit > 1) {
-        double* out = part + ((int64_t)bl * nsplit + sp) * ntiles * (GT32 * GT32) + (int64_t)tile * (GT32 * GT32);
+    // staging: thread t moves 4 columns of rows t / 4 and BM / 2 + t / 4 of each
+    // operand (four lanes read one row's 64 bytes), from clamped, in-bounds
+    // addresses (ncols is a positive multiple of 4); columns past ncols become
+    // zeros, rows past m are dropped when A is written
+    const int sr = tid >> 2, sq = tid & 3;
+    const float* rowa0 = base + (int64_t)min(ra0 + sr, m - 1) * d;
+    const float* rowa1 = base + (int64_t)min(ra0 + BM / 2 + sr, m - 1) * d;
+    const float* rowb0 = base + (int64_t)min(rb0 + sr, m - 1) * d;
+    const float* rowb1 = base + (int64_t)min(rb0 + BM / 2 + sr, m - 1) * d;
+    auto load = [&](int k0, float4 (&q)[4]) {
+        const int c = min(k0 + sq * 4, ncols - 4);
+        q[0] = *reinterpret_cast<const float4*>(rowa0 + c);
+        q[1] = *reinterpret_cast<const float4*>(rowa1 + c);
+        if (!diag_tile) {
+            q[2] = *reinterpret_cast<const float4*>(rowb0 + c);
+            q[3] = *reinterpret_cast<const float4*>(rowb1 + c);
+        }
+    };
+    auto store = [&](int buf, int k0, float4 (&q)[4]) {
+        if (k0 + SPLIT_KC > ncols) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
+            for (int i = 0; i < 4; ++i) q[i] = keep4(k0 + sq * 4 < ncols, q[i]);
+        }
+        As[buf].put4(sr, sq, q[0]);
+        As[buf].put4(BM / 2 + sr, sq, q[1]);
+        if (!diag_tile) {
+            Bs[buf].put4(sr, sq, q[2]);
+            Bs[buf].put4(BM / 2 + sr, sq, q[3]);
+        }
+    };
+
+    v16f acc[NX][NY];
 #pragma unroll
-            for (int y = 0; y < 4; ++y)
+    for (int x = 0; x < NX; ++x)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    out[(wr * 64 + x * 16 + mfma32_row(lane, r)) * GT32 + wc * 64 + y * 16 + rl] = acc[x][y][r];
-        return;
-    }
+        for (int y = 0; y < NY; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+    float4 q[4] = {};
+    load(0, q);
+    store(0, 0, q);
+    load(SPLIT_KC, q);
+    __syncthreads();
+    // Chunks k0 and k0 + 16 (zeros past ncols). The first half of the waves
+    // converts the next chunk before its MFMAs, the other half after, so that of
+    // the two waves on a SIMD one converts while the other multiplies; each
+    // loads the chunk after that at once, a whole step ahead of its conversion.
+    const bool early = wave < NT / 128;
+    auto walk = [&](auto all) {
+        auto step = [&](int buf, int k0) {
+            if (early) {
+                store(buf ^ 1, k0 + SPLIT_KC, q);
+                load(k0 + 2 * SPLIT_KC, q);
+            }
+            split_mma<decltype(all)::value>(As[buf], diag_tile ? As[buf] : Bs[buf], wr * WM, wc * WN, lane, on, acc);
+            if (!early) {
+                store(buf ^ 1, k0 + SPLIT_KC, q);
+                load(k0 + 2 * SPLIT_KC, q);
+            }
+            __syncthreads();
+        };
+        for (int k0 = 0; k0 < ncols; k0 += 2 * SPLIT_KC) {
+            step(0, k0);
+            step(1, k0 + SPLIT_KC);
+        }
+    };
+    // the same for the whole work-group
+    if (!diag_tile && ra0 + BM <= m)
+        walk(std::true_type{});
+    else
+        walk(std::false_type{});
+    double* out = part + (((int64_t)bl * nsplit + sp) * ntiles + tile) * (BM * BM);
     float* Ab = A + (int64_t)bl * mp * mp;
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int x = 0; x < NX; ++x)
 #pragma unroll
-        for (int y = 0; y < 4; ++y)
+        for (int y = 0; y < NY; ++y) {
+            if (ra0 + wr * WM + 32 * x < rb0 + wc * WN + 32 * y) continue;  // wholly above the diagonal
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = ra0 + wr * 64 + x * 16 + mfma32_row(lane, r);
-                const int col = rb0 + wc * 64 + y * 16 + rl;
-                if (row < mp && col < mp) {
-                    double v = (double)acc[x][y][r];
-                    if (row == col) v += (row < m) ? mu : 1.0;
-                    Ab[(int64_t)row * mp + col] = (float)v;
-                }
+            for (int r = 0; r < 16; ++r) {
+                const int rr = wr * WM + x * 32 + mfma32x32_row(lane, r), cc = wc * WN + y * 32 + (lane & 31);
+                const int row = ra0 + rr, col = rb0 + cc;
+                if (row >= mp || col >= mp) continue;
+                const double v = row < m && col < m ? (double)acc[x][y][r] : 0.0;
+                if (nsplit > 1)
+                    out[rr * BM + cc] = v;
+                else
+                    Ab[(int64_t)row * mp + col] = (float)(row == col ? v + (row < m ? mu : 1.0) : v);
             }
+        }
 }
 
 }  // namespace
@@ -569,11 +579,15 @@ int gram_blocks_splits(int nb, int mp, int B, int& ntiles, int& kcols) {
     return (int)ceil_div(B, kcols);
 }
 
-// Column splits of the fp32 kernel: at most SPLIT32 columns each (fp32 sums
-// stay short), and more when a batch has fewer tiles than CUs (splits of at
-// least SPLIT32 columns, up to ~1024 work-groups).
+// Tile edge of the fast mode's Gram: 256 (one work-group per CU, half the
+// operand traffic), or 128 where 256-tiles would be mostly padding.
+int gram32_tile(int mp) { return mp <= 128 ? 128 : 256; }
+
+// Column splits of the fast mode's Gram: at most SPLIT32 columns each (fp32
+// sums stay short), and more when a batch has fewer tiles than CUs (splits of
+// at least SPLIT32 columns, up to ~1024 work-groups).
 int gram32_splits(int nb, int mp, int B, int& ntiles, int& kcols) {
-    const int T = (int)ceil_div(mp, GT32);
+    const int T = (int)ceil_div(mp, gram32_tile(mp));
     ntiles = T * (T + 1) / 2;
     const int64_t wgs = (int64_t)nb * ntiles;
     int64_t ns = ceil_div(B, SPLIT32);
@@ -583,15 +597,15 @@ int gram32_splits(int nb, int mp, int B, int& ntiles, int& kcols) {
         if (fill > ns) ns = fill;
     }
     if (ns < 1) ns = 1;
-    kcols = (int)round_up(ceil_div(B, ns), KB32);
+    kcols = (int)round_up(ceil_div(B, ns), KB);
     return (int)ceil_div(B, kcols);
 }
 }  // namespace
 
 int64_t gram_blocks32_part_doubles(int nb, int mp, int B) {
     int ntiles, kcols;
-    const int ns = gram32_splits(nb, mp, B, ntiles, kcols);
-    return ns > 1 ? (int64_t)nb * ns * ntiles * (GT32 * GT32) : 0;
+    const int ns = gram32_splits(nb, mp, B, ntiles, kcols), tile = gram32_tile(mp);
+    return ns > 1 ? (int64_t)nb * ns * ntiles * (tile * tile) : 0;
 }
 
 int64_t gram_blocks_part_doubles(int nb, int mp, int B) {
@@ -600,17 +614,26 @@ int64_t gram_blocks_part_doubles(int nb, int mp, int B) {
     return ns > 1 ? (int64_t)nb * ns * ntiles * (GT * GT) : 0;
 }
 
-hipError_t launch_gram_blocks32(const float* G, int m, int64_t d, int B, int b0, int nb, double mu, float* A,
-                                int mp, double* part, hipStream_t st) {
+namespace {
+template <int BM, int WM, int WN>
+hipError_t gram_blocks32_tile(const float* G, int m, int64_t d, int B, int b0, int nb, double mu, float* A, int mp,
+                              double* part, hipStream_t st) {
     int ntiles, kcols;
     const int ns = gram32_splits(nb, mp, B, ntiles, kcols);
-    hipLaunchKernelGGL(k_gram_blocks32, dim3((unsigned)(ntiles * ns * nb)), dim3(1024), 0, st, G, m, d, B, b0, ntiles,
-                       ns, kcols, mu, A, mp, part);
+    hipLaunchKernelGGL((k_gram_blocks32<BM, WM, WN>), dim3((unsigned)(ntiles * ns * nb)), dim3(BM * 2), 0, st, G, m, d,
+                       B, b0, ntiles, ns, kcols, mu, A, mp, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ns == 1) return e;
-    hipLaunchKernelGGL((k_gram_blocks_reduce<float, GT32>), dim3((unsigned)ntiles, (unsigned)nb, GT32 * GT32 / 32),
+    hipLaunchKernelGGL((k_gram_blocks_reduce<float, BM>), dim3((unsigned)ntiles, (unsigned)nb, BM * BM / 32),
                        dim3(256), 0, st, part, ns, ntiles, m, mu, 0, A, mp);
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_gram_blocks32(const float* G, int m, int64_t d, int B, int b0, int nb, double mu, float* A,
+                                int mp, double* part, hipStream_t st) {
+    if (gram32_tile(mp) == 128) return gram_blocks32_tile<128, 64, 64>(G, m, d, B, b0, nb, mu, A, mp, part, st);
+    return gram_blocks32_tile<256, 128, 64>(G, m, d, B, b0, nb, mu, A, mp, part, st);
 }
 
 hipError_t launch_gram_blocks(const float* G, int m, int64_t d, int B, int b0, int nb, double mu,

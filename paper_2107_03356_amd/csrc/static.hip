@@ -16,7 +16,10 @@
 // then an 8-pass radix selection of the keep-th largest key (8-bit digits of
 // the IEEE bit pattern, which orders non-negative doubles), then a mask pass
 // that ranks exact ties by index with a deterministic chunked scan.
+#include <type_traits>
+
 #include "internal.h"
+#include "split_mfma.h"
 #include "tile_util.h"
 
 namespace mfac {
@@ -148,131 +151,145 @@ __global__ __launch_bounds__(512, 4) void k_trmm_diag(const double* __restrict__
         diag[(int64_t)b * B + c0 + tid] = (1.0 - ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]))) * inv_lam;
 }
 
-// fp32 MFMA variant (v_mfma_f32_16x16x4f32) for the fast static mode: the
-// same walk as k_trmm_diag, 32-deep k-chunks of fp32 operands in LDS ([row][k]
-// for L^-1 with a 36-float pitch, [k][column] for G with a 144-float pitch:
-// the 16-row x 4-k and 4-k x 16-column read patterns of one MFMA operand hit
-// distinct banks), L^-1 the fp32 factor's output. G is only read. W is
-// stored (fp32, row stride d) when Wout is set; the column sums of squares of
-// the fp32 W values are summed in fp64 and give the diagonal when diag is set.
-constexpr int TK32 = 32;
-constexpr int PA32 = TK32 + 4;   // [row][k] pitch (floats)
-constexpr int PB32 = TN + 16;    // [k][column] pitch (floats)
-
-__global__ __launch_bounds__(512, 2) void k_trmm32(const float* __restrict__ Linv, int mp, int64_t lstride,
-                                                   const float* __restrict__ G, int m, int64_t d, int B, int b0,
-                                                   int nslice, double inv_lam, double* __restrict__ diag,
-                                                   float* __restrict__ Wout) {
-    __shared__ float As[2][TM][PA32];
-    __shared__ float Bs[2][TK32][PB32];
-    __shared__ double red[4][TN];
+// The same product for the fast static mode, W = L^-1 G_b with fp32 products on
+// the bf16 matrix cores (split_mfma.h), L^-1 the fp32 factor's output. G is only
+// read. W is stored (fp32, row stride d) when Wout is set; the column sums of
+// squares of the fp32 W values are summed in fp64 and give the diagonal when
+// diag is set. A work-group owns a BN-column slice of one block and walks its
+// BN-row tiles; waves of WM x WN, 16-deep k-chunks double-buffered in LDS and
+// converted as they are staged, the schedule of k_gram_blocks32. 32 x 32 pieces past row m or column ncol are skipped, and in
+// the diagonal tile a piece stops at its own rows (L^-1 is zero right of them;
+// its upper 64-tiles are not defined, and no piece reads them). Waves w and w + 4
+// of a 256-tile share a SIMD (round-robin placement): upper and lower rows are
+// paired there, which balances the skipped chunks.
+template <int BN, int WM, int WN>
+__global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, 2) void k_trmm32(
+    const float* __restrict__ Linv, int mp, int64_t lstride, const float* __restrict__ G, int m, int64_t d, int B,
+    int b0, int nslice, double inv_lam, double* __restrict__ diag, float* __restrict__ Wout) {
+    constexpr int NX = WM / 32, NY = WN / 32, NT = (BN / WM) * (BN / WN) * 64;
+    static_assert(NT == BN * 2, "two 4-value pieces of L^-1 and one 8-value piece of G per thread");
+    __shared__ SplitChunk<BN> As[2], Bs[2];
+    __shared__ double red[BN / WM][BN];
     const int lid = xcd_remap(blockIdx.x, gridDim.x);
     const int bl = lid / nslice, sl = lid - (lid / nslice) * nslice;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // wave -> 32 x 64 piece (rows wr*32, columns wc*64). Waves w and w+4 share
-    // a SIMD (round-robin placement); pairing row pieces {0, 3} and {1, 2}
-    // there balances the chunks skipped in the diagonal 128-block below.
-    const int wr = (wave & 2) ? ((wave & 4) ? 2 : 1) : ((wave & 4) ? 3 : 0);
-    const int wc = wave & 1;
-    const int rl = lane & 15, kl = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave / (BN / WN), wc = wave % (BN / WN);  // rows wr * WM, columns wc * WN
     const int b = b0 + bl;
-    const int c0 = sl * TN;
-    const int ncol = (B - c0) < TN ? (B - c0) : TN;
+    const int c0 = sl * BN;
+    const int ncol = (B - c0) < BN ? (B - c0) : BN;
     const float* __restrict__ Lb = Linv + (int64_t)bl * lstride;
     const float* __restrict__ Gb = G + (int64_t)b * B + c0;
-    const int T = (mp + TM - 1) / TM;
+    const int T = (m + BN - 1) / BN;
 
-    // staging of one k-chunk: L^-1 rows [r0, r0+128) x k [k0, k0+32), 8 per
-    // thread (row tid/4, k (tid%4)*8 .. +7); G rows [k0, k0+32) x 128 columns,
-    // 8 per thread (row tid/16, columns (tid%16)*8 .. +7)
-    const int ar = tid >> 2, ac = (tid & 3) * 8;
-    const int br = tid >> 4, bc = (tid & 15) * 8;
-    // each float4 clamped on its own (ncol is a multiple of 4): the quads
-    // inside the slice load their own columns, the others in-bounds data that
-    // lands in columns nothing reads
-    const int bc0 = min(bc, ncol - 4), bc1 = min(bc + 4, ncol - 4);
-    float4 ra0, ra1, rb0, rb1;
-    auto load = [&](int r0, int k0) {
-        const int64_t arow = (int64_t)min(r0 + ar, mp - 1) * mp + k0 + ac;
-        const float4* p = reinterpret_cast<const float4*>(Lb + arow);
-        ra0 = p[0];
-        ra1 = p[1];
-        const float* gp = Gb + (int64_t)min(k0 + br, m - 1) * d;
-        rb0 = *reinterpret_cast<const float4*>(gp + bc0);
-        rb1 = *reinterpret_cast<const float4*>(gp + bc1);
-    };
-    auto store = [&](int buf) {
-        float4* a = reinterpret_cast<float4*>(&As[buf][ar][ac]);
-        a[0] = ra0;
-        a[1] = ra1;
-        float4* q = reinterpret_cast<float4*>(&Bs[buf][br][bc]);
-        q[0] = rb0;
-        q[1] = rb1;
-    };
-
-    double sq[4] = {0.0, 0.0, 0.0, 0.0};
+    // staging of one k-chunk: L^-1, k 4 (tid % 4) .. +3 of rows tid / 4 and
+    // BN / 2 + tid / 4; G, k 8 (tid / BN) .. +7 of column tid % BN. Clamped,
+    // in-bounds addresses: rows of L^-1 past mp and columns past the slice land in
+    // pieces that are skipped or dropped, rows of G past m meet the zeros right
+    // of L^-1's diagonal.
+    const int sr = tid >> 2, sq = tid & 3;
+    const int gc = tid % BN, gh = wave * 64 / BN;
+    const unsigned gcc = (unsigned)min(gc, ncol - 1);
+    double sqs[NY];
+#pragma unroll
+    for (int y = 0; y < NY; ++y) sqs[y] = 0.0;
     for (int r = T - 1; r >= 0; --r) {
-        v4f acc[2][4];
+        const float* __restrict__ l0 = Lb + (int64_t)min(r * BN + sr, mp - 1) * mp + sq * 4;
+        const float* __restrict__ l1 = Lb + (int64_t)min(r * BN + BN / 2 + sr, mp - 1) * mp + sq * 4;
+        struct Stage {
+            float4 a0, a1;
+            f8v g;
+        };
+        auto load = [&](int k0, Stage& q) {
+            const int kl = min(k0, mp - SPLIT_KC);
+            q.a0 = *reinterpret_cast<const float4*>(l0 + kl);
+            q.a1 = *reinterpret_cast<const float4*>(l1 + kl);
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+            for (int i = 0; i < 8; ++i) q.g[i] = (Gb + (int64_t)min(k0 + gh * 8 + i, m - 1) * d)[gcc];
+        };
+        auto store = [&](int buf, const Stage& q) {
+            As[buf].put4(sr, sq, q.a0);
+            As[buf].put4(BN / 2 + sr, sq, q.a1);
+            Bs[buf].put8(gc, gh, q.g);
+        };
+        v16f acc[NX][NY];
+        unsigned on = 0;  // pieces with rows below m and columns in the slice
 #pragma unroll
-            for (int y = 0; y < 4; ++y) acc[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
-        const int khi = min((r + 1) * TM, mp);
-        const int nchunk = khi / TK32;
-        load(r * TM, 0);
-        store(0);
-        __syncthreads();
-        for (int c = 0; c < nchunk; ++c) {
-            const int buf = c & 1;
-            if (c + 1 < nchunk) load(r * TM, (c + 1) * TK32);
-            // L^-1 is zero right of this wave's rows: chunks wholly there add nothing
-            if (c * TK32 < r * TM + wr * 32 + 32) {
+        for (int x = 0; x < NX; ++x)
 #pragma unroll
-                for (int kk = 0; kk < TK32 / 4; ++kk) {
-                    float av[2], bv[4];
+            for (int y = 0; y < NY; ++y) {
 #pragma unroll
-                    for (int x = 0; x < 2; ++x) av[x] = As[buf][wr * 32 + x * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                    for (int y = 0; y < 4; ++y) bv[y] = Bs[buf][kk * 4 + kl][wc * 64 + y * 16 + rl];
-#pragma unroll
-                    for (int x = 0; x < 2; ++x)
-#pragma unroll
-                        for (int y = 0; y < 4; ++y)
-                            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[x], bv[y], acc[x][y], 0, 0, 0);
-                }
+                for (int q = 0; q < 16; ++q) acc[x][y][q] = 0.f;
+                if (r * BN + wr * WM + 32 * x < m && wc * WN + 32 * y < ncol) on |= 1u << (x * NY + y);
             }
-            if (c + 1 < nchunk) store(buf ^ 1);
+        Stage q;
+        load(0, q);
+        store(0, q);
+        load(SPLIT_KC, q);
+        __syncthreads();
+        const bool early = wave < NT / 128;
+        auto step = [&](auto all, unsigned mask, int buf, int k0) {
+            if (early) {
+                store(buf ^ 1, q);
+                load(k0 + 2 * SPLIT_KC, q);
+            }
+            split_mma<decltype(all)::value>(As[buf], Bs[buf], wr * WM, wc * WN, lane, mask, acc);
+            if (!early) {
+                store(buf ^ 1, q);
+                load(k0 + 2 * SPLIT_KC, q);
+            }
             __syncthreads();
+        };
+        // left of the diagonal tile (the same choice for the whole work-group)
+        int k0 = 0;
+        if ((r + 1) * BN <= m && ncol == BN) {
+            for (; k0 < r * BN; k0 += 2 * SPLIT_KC) {
+                step(std::true_type{}, on, 0, k0);
+                step(std::true_type{}, on, 1, k0 + SPLIT_KC);
+            }
+        }
+        // the diagonal tile (all chunks of a ragged one): piece x up to k = its last row
+        auto below = [&](int k) {
+            unsigned mk = 0;
+#pragma unroll
+            for (int x = 0; x < NX; ++x)
+                if (k < r * BN + wr * WM + 32 * x + 32) mk |= ((1u << NY) - 1) << (x * NY);
+            return on & mk;
+        };
+        const int khi = min((r + 1) * BN, mp);
+        for (; k0 < khi; k0 += 2 * SPLIT_KC) {
+            step(std::false_type{}, below(k0), 0, k0);
+            step(std::false_type{}, below(k0 + SPLIT_KC), 1, k0 + SPLIT_KC);
         }
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < NX; ++x)
 #pragma unroll
-            for (int y = 0; y < 4; ++y)
+            for (int y = 0; y < NY; ++y)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int row = r * TM + wr * 32 + x * 16 + mfma32_row(lane, q);
-                    const int col = wc * 64 + y * 16 + rl;
+                for (int q = 0; q < 16; ++q) {
+                    const int row = r * BN + wr * WM + x * 32 + mfma32x32_row(lane, q);
+                    const int col = wc * WN + y * 32 + (lane & 31);
                     const float w = acc[x][y][q];
                     if (row < m) {
-                        sq[y] += (double)w * (double)w;
+                        sqs[y] += (double)w * (double)w;
                         if (Wout && col < ncol) Wout[(int64_t)row * d + (int64_t)b * B + c0 + col] = w;
                     }
                 }
     }
     if (!diag) return;
-    // column sums of squares: over the lanes of one column (+16, +32), then over the four wr
+    // column sums of squares: over the two lanes of one column, then over the wr
 #pragma unroll
-    for (int y = 0; y < 4; ++y) {
-        sq[y] += __shfl_xor(sq[y], 16, 64);
-        sq[y] += __shfl_xor(sq[y], 32, 64);
-    }
-    if (kl == 0) {
-#pragma unroll
-        for (int y = 0; y < 4; ++y) red[wr][wc * 64 + y * 16 + rl] = sq[y];
+    for (int y = 0; y < NY; ++y) {
+        sqs[y] += __shfl_xor(sqs[y], 32, 64);
+        if (lane < 32) red[wr][wc * WN + y * 32 + lane] = sqs[y];
     }
     __syncthreads();
-    if (tid < ncol)
-        diag[(int64_t)b * B + c0 + tid] = (1.0 - ((red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]))) * inv_lam;
+    if (tid < ncol) {
+        double s = red[0][tid];
+#pragma unroll
+        for (int i = 1; i < BN / WM; ++i) s += red[i][tid];
+        diag[(int64_t)b * B + c0 + tid] = (1.0 - s) * inv_lam;
+    }
 }
 
 __global__ void k_diag_to_f32(const double* __restrict__ dg, int64_t d, float* __restrict__ out) {
@@ -974,9 +991,16 @@ hipError_t launch_trmm_diag(const double* Linv, int mp, int64_t bstride, float* 
 
 hipError_t launch_trmm32(const float* Linv, int mp, int64_t lstride, const float* G, int m, int64_t d, int B, int b0,
                          int nb, double lam, double* diag, float* Wout, hipStream_t st) {
-    const int nslice = (int)ceil_div(B, TN);
-    hipLaunchKernelGGL(k_trmm32, dim3((unsigned)(nslice * nb)), dim3(512), 0, st, Linv, mp, lstride, G, m, d, B, b0,
-                       nslice, 1.0 / lam, diag, Wout);
+    // 128-tiles where a 256-tile would be mostly padding
+    if (mp <= 128 || B <= 128) {
+        const int nslice = (int)ceil_div(B, 128);
+        hipLaunchKernelGGL((k_trmm32<128, 64, 64>), dim3((unsigned)(nslice * nb)), dim3(256), 0, st, Linv, mp, lstride,
+                           G, m, d, B, b0, nslice, 1.0 / lam, diag, Wout);
+    } else {
+        const int nslice = (int)ceil_div(B, 256);
+        hipLaunchKernelGGL((k_trmm32<256, 128, 64>), dim3((unsigned)(nslice * nb)), dim3(512), 0, st, Linv, mp,
+                           lstride, G, m, d, B, b0, nslice, 1.0 / lam, diag, Wout);
+    }
     return hipGetLastError();
 }
 

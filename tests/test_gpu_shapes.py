@@ -57,3 +57,38 @@ def test_wide_block_gram_reduction(dev, d, m):
     diag = sb.inv_diag(fp64=True).cpu().numpy()
     assert sb.status() == 0
     assert np.max(np.abs(diag / ostatic.inv_diag(G.numpy(), 1e-4, d) - 1.0)) < 1e-11
+
+
+# fast mode: m and B on both sides of the 32-row pieces, the 64-row padding, the
+# 128- and 256-row tiles, 16-column chunks in odd number, a split block (B > 2048)
+FAST_SHAPES = [(1, 4, 3), (31, 20, 5), (33, 36, 4), (64, 128, 3), (65, 132, 3), (128, 256, 2), (129, 260, 2),
+               (255, 300, 2), (256, 256, 2), (257, 512, 2), (320, 1040, 2), (513, 2048, 1), (200, 2052, 1),
+               (130, 4100, 2)]
+
+
+@pytest.mark.parametrize("m,B,nb", FAST_SHAPES)
+def test_fast_gram_and_w(dev, m, B, nb):
+    """The inverse diagonal (Gram, factor, W) and the IHVP of a second block.
+
+    S_j = 1 - lam * diag_j is a sum of m squares of W, each with the rounding of
+    fp32 sums over k <= max(m, 2048) terms: (sqrt(k) + 2) 2^-24 relative at
+    most for well-conditioned blocks, 1e-6 at these sizes with a factor of two.
+    """
+    from paper_2107_03356_amd import StaticBlocks
+    say("fast shapes", m, B, nb)
+    base = get_workload("static_d4.19m_b2048_m1024")
+    wl = base.scaled(d=B * nb, m=m, block=B, lam=1e-4, scale_d=base.d)
+    gs = GradientStream(wl, seed=m + B)
+    G = gs.rows(0, m)
+    Gd = G.to(dev).contiguous()
+    sb = StaticBlocks(Gd, B, wl.lam, fp32=True)
+    S = 1.0 - wl.lam * sb.inv_diag(fp64=True).cpu().numpy()
+    X = gs.queries(0, 1)
+    Y = sb.ihvp(X.to(dev)).cpu().numpy()[0]
+    assert sb.status() == 0
+    assert np.array_equal(Gd.cpu().numpy(), G.numpy())
+    Sref = 1.0 - wl.lam * ostatic.inv_diag(G.numpy(), wl.lam, B)
+    # 1 - lam diag itself carries fp64 rounding of 1
+    assert np.max(np.abs(S - Sref) / (np.abs(Sref) + 1e-9)) < 4e-6
+    assert rel_l2(S, Sref) < 1e-6
+    assert rel_l2(Y, ostatic.ihvp(G.numpy(), wl.lam, B, X.numpy())[0]) < 1e-6
