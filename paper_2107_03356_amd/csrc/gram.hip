@@ -390,11 +390,11 @@ __global__ __launch_bounds__(256) void k_gram_blocks_reduce(const double* __rest
 constexpr int SPLIT32 = 2048;
 
 template <int BM, int WM, int WN>
-__global__ __launch_bounds__((BM / WM) * (BM / WN) * 64, 2) void k_gram_blocks32(
+__global__ __launch_bounds__((BM / WM) * (BM / WN) * 64, BM == 128 ? 4 : 2) void k_gram_blocks32(
     const float* __restrict__ G, int m, int64_t d, int B, int b0, int ntiles, int nsplit, int kcols, double mu,
     float* __restrict__ A, int mp, double* __restrict__ part) {
     constexpr int NX = WM / 32, NY = WN / 32, NT = (BM / WM) * (BM / WN) * 64;
-    static_assert(NT == BM * 2, "two 4-value pieces per thread and operand");
+    constexpr int RPT = BM * 4 / NT;  // rows (4 columns each) a thread stages per operand and chunk
     __shared__ SplitChunk<BM> As[2], Bs[2];
     const int lid = xcd_remap(blockIdx.x, gridDim.x);
     const int per_block = ntiles * nsplit;
@@ -431,34 +431,37 @@ __global__ __launch_bounds__((BM / WM) * (BM / WN) * 64, 2) void k_gram_blocks32
             const int r = ra0 + wr * WM + 32 * x, c = rb0 + wc * WN + 32 * y;
             if (r < m && c < m && r >= c) on |= 1u << (x * NY + y);
         }
-    // staging: thread t moves 4 columns of rows t / 4 and BM / 2 + t / 4 of each
-    // operand (four lanes read one row's 64 bytes), from clamped, in-bounds
-    // addresses (ncols is a positive multiple of 4); columns past ncols become
-    // zeros, rows past m are dropped when A is written
+    // staging: thread t moves 4 columns of rows t / 4 + i NT / 4 of each operand
+    // (four lanes read one row's 64 bytes), from clamped, in-bounds addresses
+    // (ncols is a positive multiple of 4); columns past ncols become zeros, rows
+    // past m are dropped when A is written
     const int sr = tid >> 2, sq = tid & 3;
-    const float* rowa0 = base + (int64_t)min(ra0 + sr, m - 1) * d;
-    const float* rowa1 = base + (int64_t)min(ra0 + BM / 2 + sr, m - 1) * d;
-    const float* rowb0 = base + (int64_t)min(rb0 + sr, m - 1) * d;
-    const float* rowb1 = base + (int64_t)min(rb0 + BM / 2 + sr, m - 1) * d;
-    auto load = [&](int k0, float4 (&q)[4]) {
+    const float* row[2 * RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        row[i] = base + (int64_t)min(ra0 + sr + i * (NT / 4), m - 1) * d;
+        row[RPT + i] = base + (int64_t)min(rb0 + sr + i * (NT / 4), m - 1) * d;
+    }
+    float4 q[2 * RPT] = {};
+    auto load = [&](int k0) {
         const int c = min(k0 + sq * 4, ncols - 4);
-        q[0] = *reinterpret_cast<const float4*>(rowa0 + c);
-        q[1] = *reinterpret_cast<const float4*>(rowa1 + c);
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) q[i] = *reinterpret_cast<const float4*>(row[i] + c);
         if (!diag_tile) {
-            q[2] = *reinterpret_cast<const float4*>(rowb0 + c);
-            q[3] = *reinterpret_cast<const float4*>(rowb1 + c);
+#pragma unroll
+            for (int i = RPT; i < 2 * RPT; ++i) q[i] = *reinterpret_cast<const float4*>(row[i] + c);
         }
     };
-    auto store = [&](int buf, int k0, float4 (&q)[4]) {
+    auto store = [&](int buf, int k0) {
         if (k0 + SPLIT_KC > ncols) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) q[i] = keep4(k0 + sq * 4 < ncols, q[i]);
+            for (int i = 0; i < 2 * RPT; ++i) q[i] = keep4(k0 + sq * 4 < ncols, q[i]);
         }
-        As[buf].put4(sr, sq, q[0]);
-        As[buf].put4(BM / 2 + sr, sq, q[1]);
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) As[buf].put4(sr + i * (NT / 4), sq, q[i]);
         if (!diag_tile) {
-            Bs[buf].put4(sr, sq, q[2]);
-            Bs[buf].put4(BM / 2 + sr, sq, q[3]);
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) Bs[buf].put4(sr + i * (NT / 4), sq, q[RPT + i]);
         }
     };
 
@@ -469,10 +472,9 @@ __global__ __launch_bounds__((BM / WM) * (BM / WN) * 64, 2) void k_gram_blocks32
         for (int y = 0; y < NY; ++y)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-    float4 q[4] = {};
-    load(0, q);
-    store(0, 0, q);
-    load(SPLIT_KC, q);
+    load(0);
+    store(0, 0);
+    load(SPLIT_KC);
     __syncthreads();
     // Chunks k0 and k0 + 16 (zeros past ncols). The first half of the waves
     // converts the next chunk before its MFMAs, the other half after, so that of
@@ -482,13 +484,13 @@ __global__ __launch_bounds__((BM / WM) * (BM / WN) * 64, 2) void k_gram_blocks32
     auto walk = [&](auto all) {
         auto step = [&](int buf, int k0) {
             if (early) {
-                store(buf ^ 1, k0 + SPLIT_KC, q);
-                load(k0 + 2 * SPLIT_KC, q);
+                store(buf ^ 1, k0 + SPLIT_KC);
+                load(k0 + 2 * SPLIT_KC);
             }
             split_mma<decltype(all)::value>(As[buf], diag_tile ? As[buf] : Bs[buf], wr * WM, wc * WN, lane, on, acc);
             if (!early) {
-                store(buf ^ 1, k0 + SPLIT_KC, q);
-                load(k0 + 2 * SPLIT_KC, q);
+                store(buf ^ 1, k0 + SPLIT_KC);
+                load(k0 + 2 * SPLIT_KC);
             }
             __syncthreads();
         };
@@ -620,7 +622,8 @@ hipError_t gram_blocks32_tile(const float* G, int m, int64_t d, int B, int b0, i
                               double* part, hipStream_t st) {
     int ntiles, kcols;
     const int ns = gram32_splits(nb, mp, B, ntiles, kcols);
-    hipLaunchKernelGGL((k_gram_blocks32<BM, WM, WN>), dim3((unsigned)(ntiles * ns * nb)), dim3(BM * 2), 0, st, G, m, d,
+    hipLaunchKernelGGL((k_gram_blocks32<BM, WM, WN>), dim3((unsigned)(ntiles * ns * nb)),
+                       dim3((BM / WM) * (BM / WN) * 64), 0, st, G, m, d,
                        B, b0, ntiles, ns, kcols, mu, A, mp, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ns == 1) return e;
@@ -632,7 +635,7 @@ hipError_t gram_blocks32_tile(const float* G, int m, int64_t d, int B, int b0, i
 
 hipError_t launch_gram_blocks32(const float* G, int m, int64_t d, int B, int b0, int nb, double mu, float* A,
                                 int mp, double* part, hipStream_t st) {
-    if (gram32_tile(mp) == 128) return gram_blocks32_tile<128, 64, 64>(G, m, d, B, b0, nb, mu, A, mp, part, st);
+    if (gram32_tile(mp) == 128) return gram_blocks32_tile<128, 32, 64>(G, m, d, B, b0, nb, mu, A, mp, part, st);
     return gram_blocks32_tile<256, 128, 64>(G, m, d, B, b0, nb, mu, A, mp, part, st);
 }
 

@@ -163,11 +163,11 @@ __global__ __launch_bounds__(512, 4) void k_trmm_diag(const double* __restrict__
 // of a 256-tile share a SIMD (round-robin placement): upper and lower rows are
 // paired there, which balances the skipped chunks.
 template <int BN, int WM, int WN>
-__global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, 2) void k_trmm32(
+__global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, BN == 128 ? 4 : 2) void k_trmm32(
     const float* __restrict__ Linv, int mp, int64_t lstride, const float* __restrict__ G, int m, int64_t d, int B,
     int b0, int nslice, double inv_lam, double* __restrict__ diag, float* __restrict__ Wout) {
     constexpr int NX = WM / 32, NY = WN / 32, NT = (BN / WM) * (BN / WN) * 64;
-    static_assert(NT == BN * 2, "two 4-value pieces of L^-1 and one 8-value piece of G per thread");
+    constexpr int RPT = BN * 4 / NT;  // 4-value pieces of L^-1 and of G a thread stages per chunk
     __shared__ SplitChunk<BN> As[2], Bs[2];
     __shared__ double red[BN / WM][BN];
     const int lid = xcd_remap(blockIdx.x, gridDim.x);
@@ -182,11 +182,11 @@ __global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, 2) void k_trmm32(
     const float* __restrict__ Gb = G + (int64_t)b * B + c0;
     const int T = (m + BN - 1) / BN;
 
-    // staging of one k-chunk: L^-1, k 4 (tid % 4) .. +3 of rows tid / 4 and
-    // BN / 2 + tid / 4; G, k 8 (tid / BN) .. +7 of column tid % BN. Clamped,
-    // in-bounds addresses: rows of L^-1 past mp and columns past the slice land in
-    // pieces that are skipped or dropped, rows of G past m meet the zeros right
-    // of L^-1's diagonal.
+    // staging of one k-chunk: L^-1, k 4 (tid % 4) .. +3 of rows tid / 4 + i NT / 4;
+    // G, 4 RPT k from 4 RPT (tid / BN) on of column tid % BN. Clamped, in-bounds
+    // addresses: rows of L^-1 past mp and columns past the slice land in pieces
+    // that are skipped or dropped, rows of G past m meet the zeros right of
+    // L^-1's diagonal.
     const int sr = tid >> 2, sq = tid & 3;
     const int gc = tid % BN, gh = wave * 64 / BN;
     const unsigned gcc = (unsigned)min(gc, ncol - 1);
@@ -194,23 +194,30 @@ __global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, 2) void k_trmm32(
 #pragma unroll
     for (int y = 0; y < NY; ++y) sqs[y] = 0.0;
     for (int r = T - 1; r >= 0; --r) {
-        const float* __restrict__ l0 = Lb + (int64_t)min(r * BN + sr, mp - 1) * mp + sq * 4;
-        const float* __restrict__ l1 = Lb + (int64_t)min(r * BN + BN / 2 + sr, mp - 1) * mp + sq * 4;
-        struct Stage {
-            float4 a0, a1;
-            f8v g;
-        };
-        auto load = [&](int k0, Stage& q) {
-            const int kl = min(k0, mp - SPLIT_KC);
-            q.a0 = *reinterpret_cast<const float4*>(l0 + kl);
-            q.a1 = *reinterpret_cast<const float4*>(l1 + kl);
+        const float* __restrict__ lrow[RPT];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) q.g[i] = (Gb + (int64_t)min(k0 + gh * 8 + i, m - 1) * d)[gcc];
+        for (int i = 0; i < RPT; ++i) lrow[i] = Lb + (int64_t)min(r * BN + sr + i * (NT / 4), mp - 1) * mp + sq * 4;
+        float4 qa[RPT], qg[RPT];
+        auto load = [&](int k0) {
+            const int kl = min(k0, mp - SPLIT_KC);
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) qa[i] = *reinterpret_cast<const float4*>(lrow[i] + kl);
+            auto g = [&](int k) { return (Gb + (int64_t)min(k, m - 1) * d)[gcc]; };
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                const int k = k0 + (gh * RPT + i) * 4;
+                qg[i] = make_float4(g(k), g(k + 1), g(k + 2), g(k + 3));
+            }
         };
-        auto store = [&](int buf, const Stage& q) {
-            As[buf].put4(sr, sq, q.a0);
-            As[buf].put4(BN / 2 + sr, sq, q.a1);
-            Bs[buf].put8(gc, gh, q.g);
+        auto store = [&](int buf) {
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) As[buf].put4(sr + i * (NT / 4), sq, qa[i]);
+            if constexpr (RPT == 2) {
+                Bs[buf].put8(gc, gh, f8v{qg[0].x, qg[0].y, qg[0].z, qg[0].w, qg[1].x, qg[1].y, qg[1].z, qg[1].w});
+            } else {
+#pragma unroll
+                for (int i = 0; i < RPT; ++i) Bs[buf].put4(gc, gh * RPT + i, qg[i]);
+            }
         };
         v16f acc[NX][NY];
         unsigned on = 0;  // pieces with rows below m and columns in the slice
@@ -222,21 +229,20 @@ __global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, 2) void k_trmm32(
                 for (int q = 0; q < 16; ++q) acc[x][y][q] = 0.f;
                 if (r * BN + wr * WM + 32 * x < m && wc * WN + 32 * y < ncol) on |= 1u << (x * NY + y);
             }
-        Stage q;
-        load(0, q);
-        store(0, q);
-        load(SPLIT_KC, q);
+        load(0);
+        store(0);
+        load(SPLIT_KC);
         __syncthreads();
         const bool early = wave < NT / 128;
         auto step = [&](auto all, unsigned mask, int buf, int k0) {
             if (early) {
-                store(buf ^ 1, q);
-                load(k0 + 2 * SPLIT_KC, q);
+                store(buf ^ 1);
+                load(k0 + 2 * SPLIT_KC);
             }
             split_mma<decltype(all)::value>(As[buf], Bs[buf], wr * WM, wc * WN, lane, mask, acc);
             if (!early) {
-                store(buf ^ 1, q);
-                load(k0 + 2 * SPLIT_KC, q);
+                store(buf ^ 1);
+                load(k0 + 2 * SPLIT_KC);
             }
             __syncthreads();
         };
@@ -994,7 +1000,7 @@ hipError_t launch_trmm32(const float* Linv, int mp, int64_t lstride, const float
     // 128-tiles where a 256-tile would be mostly padding
     if (mp <= 128 || B <= 128) {
         const int nslice = (int)ceil_div(B, 128);
-        hipLaunchKernelGGL((k_trmm32<128, 64, 64>), dim3((unsigned)(nslice * nb)), dim3(256), 0, st, Linv, mp, lstride,
+        hipLaunchKernelGGL((k_trmm32<128, 32, 64>), dim3((unsigned)(nslice * nb)), dim3(512), 0, st, Linv, mp, lstride,
                            G, m, d, B, b0, nslice, 1.0 / lam, diag, Wout);
     } else {
         const int nslice = (int)ceil_div(B, 256);
