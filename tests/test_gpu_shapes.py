@@ -92,3 +92,30 @@ def test_fast_gram_and_w(dev, m, B, nb):
     assert np.max(np.abs(S - Sref) / (np.abs(Sref) + 1e-9)) < 4e-6
     assert rel_l2(S, Sref) < 1e-6
     assert rel_l2(Y, ostatic.ihvp(G.numpy(), wl.lam, B, X.numpy())[0]) < 1e-6
+
+
+# every register width of the factored correction (m <= 256, 512, 1024, 2048,
+# 4096), few blocks (several shares of rows per block) and many
+@pytest.mark.parametrize("m,B,nb", [(3, 8, 5), (256, 64, 600), (300, 2048, 2), (511, 1024, 3), (1000, 500, 4),
+                                    (1025, 128, 2), (2049, 256, 2), (4096, 64, 2)])
+def test_fast_obs_update_without_and_with_w(dev, m, B, nb):
+    """The OBS correction from G and L^-1, and again from W once a query has
+    formed it. Against the oracle both carry the fp32 factor's rounding
+    (bound 4e-6: S's of test_fast_gram_and_w, and theta / diag in fp32)."""
+    from paper_2107_03356_amd import StaticBlocks
+    say("fast obs_update", m, B, nb)
+    base = get_workload("static_d4.19m_b2048_m1024")
+    wl = base.scaled(d=B * nb, m=m, block=B, lam=1e-4, scale_d=base.d)
+    gs = GradientStream(wl, seed=m + B)
+    G, theta = gs.rows(0, m), gs.theta()
+    Gd = G.to(dev).contiguous()
+    sb = StaticBlocks(Gd, B, wl.lam, fp32=True)
+    mask = (torch.arange(wl.d) % 3 != 0).to(torch.uint8)
+    d1 = sb.obs_update(theta.to(dev), mask.to(dev)).cpu().numpy()
+    sb.ihvp(gs.queries(0, 1).to(dev))
+    d2 = sb.obs_update(theta.to(dev), mask.to(dev)).cpu().numpy()
+    assert sb.status() == 0
+    assert np.array_equal(Gd.cpu().numpy(), G.numpy())
+    ref = ostatic.obs_update(G.numpy(), wl.lam, B, theta.numpy(), mask.numpy())
+    assert rel_l2(d1, ref) < 4e-6
+    assert rel_l2(d2, ref) < 4e-6
