@@ -308,76 +308,128 @@ __global__ __launch_bounds__(256) void k_pass2(const float* __restrict__ G, int 
     }
 }
 
-// Pass 2 for one vector, y = alpha x - G^T coef, m <= 4096. Work-group b
-// takes slabs b, b + gridDim.x, ...; wave w folds rows w, w + 4, ... over the
-// full slab width (8 float4 per lane), issuing the next row's loads as soon
-// as a row is folded and the next slab's first row before the slab's
-// reduction. The four fp64 column partials of a slab go through LDS (two
-// buffers, so one LDS barrier per slab) and are summed in a fixed order.
-__device__ __forceinline__ void load_slab_row(float4 (&g)[8], const float* __restrict__ G, int m, int64_t s, int i,
-                                              int lane) {
-    const float* p = G + (s * m + i) * (int64_t)SLAB + lane * 4;
+// Pass 2 for one vector, y = alpha x - G^T coef, m <= 4096. A unit is 256 U
+// columns of a slab; work-group b takes units b, b + gridDim.x, ... from the
+// last one down (pass 1 went from the first up, and the 256 MB memory-side cache
+// still holds part of what it read last: 120 -> 101 us for a 553 MB window, no
+// change at 1 GB). Wave w folds rows w, w + 4, ... over the unit's width with RB =
+// 8 / U rows in flight, loading a row's successor as soon as it is folded and
+// the next unit's first rows before the unit's reduction. Rows past m are
+// re-reads of row m - 1 with coefficient 0: a branch around a load would make
+// every later wait one for all loads (512-column units ran at a third of the
+// rate). The four fp64 column
+// partials of a unit go through LDS (two buffers, so one LDS barrier per unit)
+// and are summed in a fixed order: y does not depend on U.
+template <int U>
+struct RowUnits {
+    static constexpr int RB = 8 / U;        // rows in flight per wave
+    static constexpr int W = 256 * U;       // columns of a unit
+    static constexpr int PER = SLAB / W;    // units per slab
+    // row 0 of a unit
+    static __device__ __forceinline__ const float* base(const float* __restrict__ G, int m, int64_t unit) {
+        const int64_t s = unit / PER;
+        return G + s * m * (int64_t)SLAB + (int)(unit - s * PER) * W;
+    }
+    static __device__ __forceinline__ void load(float4 (&g)[U], const float* __restrict__ p, int i, int lane) {
+        p += (int64_t)i * SLAB;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) g[u] = ld_stream(p + u * 256);
-}
+        for (int u = 0; u < U; ++u) g[u] = ld_stream(p + u * 256 + lane * 4);
+    }
+    // column partials of one wave into its quarter of red, then the four added
+    // and handed to out(column within the unit, sums of 4 adjacent columns)
+    template <typename F>
+    static __device__ __forceinline__ void reduce(double* __restrict__ rb, const double (&acc)[U][4], int wave,
+                                                  int lane, F out);
+};
 
 // Waits for this wave's LDS operations, then for every wave of the
 // work-group; outstanding global loads stay in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-constexpr int PASS2_ROWS_MAX_M = 4096;  // m coefficients + 2 x 4 x SLAB partials = 160 KB of LDS
-constexpr int PASS2_ROWS_GRID = 256;    // one work-group per CU (the LDS holds one)
+template <int U>
+template <typename F>
+__device__ __forceinline__ void RowUnits<U>::reduce(double* __restrict__ rb, const double (&acc)[U][4], int wave,
+                                                    int lane, F out) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        double* q = rb + wave * W + u * 256 + lane * 4;
+        *reinterpret_cast<double2*>(q) = make_double2(acc[u][0], acc[u][1]);
+        *reinterpret_cast<double2*>(q + 2) = make_double2(acc[u][2], acc[u][3]);
+    }
+    lds_barrier();
+    // wave w adds columns [64 U w, 64 U (w + 1)) of the unit
+    for (int c = lane * 4; c < 64 * U; c += 256) {
+        const int col = wave * 64 * U + c;
+        double sum[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sum[k] = rb[col + k] + rb[W + col + k] + rb[2 * W + col + k] + rb[3 * W + col + k];
+        out(col, sum);
+    }
+}
 
-__global__ __launch_bounds__(256) void k_pass2_rows(const float* __restrict__ G, int m, int64_t d, int64_t nslab,
+constexpr int PASS2_ROWS_MAX_M = 4096;  // m coefficients + 2 x 4 x SLAB partials = 160 KB of LDS
+constexpr int PASS2_ROWS_GRID = 256;    // one work-group per CU (at U = 8 the LDS holds one)
+
+template <int U>
+__global__ __launch_bounds__(256) void k_pass2_rows(const float* __restrict__ G, int m, int64_t d, int64_t nunit,
                                                     const double* __restrict__ coef, VecOut vout, int aligned) {
+    using RU = RowUnits<U>;
+    constexpr int RB = RU::RB;
     extern __shared__ __align__(16) double sh[];
-    const int mpad = (m + 1) & ~1;  // keeps the partials 16-byte aligned
+    const int mr = (m + 4 * RB - 1) / (4 * RB) * (4 * RB);  // whole rounds
     double* cl = sh;
-    double* red = sh + mpad;  // [2][4][SLAB]
-    for (int t = threadIdx.x; t < m; t += 256) cl[t] = coef[t];
+    double* red = sh + mr;  // [2][4][W]
+    for (int t = threadIdx.x; t < mr; t += 256) cl[t] = t < m ? coef[t] : 0.0;
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const float alpha = vout.alpha[0];
     const float* __restrict__ x = vout.x[0];
     float* __restrict__ y = vout.y[0];
-    float4 g[8];
-    int64_t s = blockIdx.x;
-    if (s < nslab && wave < m) load_slab_row(g, G, m, s, wave, lane);
-    for (int t = 0; s < nslab; s += gridDim.x, ++t) {
-        double acc[8][4];
+    float4 g[RB][U];
+    int64_t s = nunit - 1 - (int64_t)blockIdx.x;  // grid <= nunit
+    const float* p = RU::base(G, m, s);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.0;
-        for (int i = wave; i < m; i += 4) {
-            const double cv = cl[i];
+    for (int r = 0; r < RB; ++r) RU::load(g[r], p, min(wave + 4 * r, m - 1), lane);
+    for (int t = 0; s >= 0; s -= gridDim.x, ++t) {
+        // the last unit loads its own first rows again
+        const float* pn = s >= gridDim.x ? RU::base(G, m, s - gridDim.x) : p;
+        double acc[U][4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                acc[u][0] = fma(cv, (double)g[u].x, acc[u][0]);
-                acc[u][1] = fma(cv, (double)g[u].y, acc[u][1]);
-                acc[u][2] = fma(cv, (double)g[u].z, acc[u][2]);
-                acc[u][3] = fma(cv, (double)g[u].w, acc[u][3]);
+        for (int u = 0; u < U; ++u) acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.0;
+        auto fold = [&](const float4 (&q)[U], double cv) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                acc[u][0] = fma(cv, (double)q[u].x, acc[u][0]);
+                acc[u][1] = fma(cv, (double)q[u].y, acc[u][1]);
+                acc[u][2] = fma(cv, (double)q[u].z, acc[u][2]);
+                acc[u][3] = fma(cv, (double)q[u].w, acc[u][3]);
             }
-            if (i + 4 < m)
-                load_slab_row(g, G, m, s, i + 4, lane);
-            else if (s + gridDim.x < nslab)
-                load_slab_row(g, G, m, s + gridDim.x, wave, lane);
+        };
+        if constexpr (RB == 1) {
+            // one row in flight: every wait is for all loads anyway, and the
+            // branches are cheaper than the selects (2% at d = 1M, m = 256)
+            for (int i = wave; i < m; i += 4) {
+                fold(g[0], cl[i]);
+                if (i + 4 < m)
+                    RU::load(g[0], p, i + 4, lane);
+                else if (s >= gridDim.x)
+                    RU::load(g[0], pn, wave, lane);
+            }
+        } else {
+            for (int i0 = wave; i0 < mr; i0 += 4 * RB) {
+                const bool more = i0 + 4 * RB < mr;
+                const float* pl = more ? p : pn;
+                const int il = more ? i0 + 4 * RB : wave;
+#pragma unroll
+                for (int r = 0; r < RB; ++r) {
+                    fold(g[r], cl[i0 + 4 * r]);
+                    RU::load(g[r], pl, min(il + 4 * r, m - 1), lane);
+                }
+            }
         }
-        double* rb = red + (t & 1) * 4 * SLAB;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            double* q = rb + wave * SLAB + u * 256 + lane * 4;
-            *reinterpret_cast<double2*>(q) = make_double2(acc[u][0], acc[u][1]);
-            *reinterpret_cast<double2*>(q + 2) = make_double2(acc[u][2], acc[u][3]);
-        }
-        lds_barrier();
-        // wave w writes columns [512 w, 512 w + 512) of the slab
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int col = wave * 512 + h * 256 + lane * 4;
-            const int64_t j = s * SLAB + col;
-            double sum[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                sum[k] = rb[col + k] + rb[SLAB + col + k] + rb[2 * SLAB + col + k] + rb[3 * SLAB + col + k];
+        p = pn;
+        RU::reduce(red + (t & 1) * 4 * RU::W, acc, wave, lane, [&](int col, const double (&sum)[4]) {
+            const int64_t j = s * RU::W + col;
             float4 xv = make_float4(0.f, 0.f, 0.f, 0.f);
             if (alpha != 0.f) xv = ld4(x, j, d, aligned);
             const double a = alpha;
@@ -387,7 +439,7 @@ __global__ __launch_bounds__(256) void k_pass2_rows(const float* __restrict__ G,
             o.z = (float)(a * xv.z - sum[2]);
             o.w = (float)(a * xv.w - sum[3]);
             st4_stream(y, j, d, aligned, o);
-        }
+        });
     }
 }
 
@@ -399,93 +451,89 @@ __global__ __launch_bounds__(256) void k_pass2_rows(const float* __restrict__ G,
 // knext, the slot gn will take after this pass, gets gn . gn instead of its
 // current row's dot, which makes the dots those of the window after the
 // insertion. The dots follow the precision of k_pass1 for one vector (exact
-// fp32 products summed in fp64): each wave reduces the per-lane sums of RB
+// fp32 products summed in fp64): each wave reduces the per-lane sums of 8
 // of its rows at a time across its lanes, and the work-group keeps fp64 row
 // sums in LDS, written out in the partial layout of k_pass1 (one row group).
 constexpr int PASS21_RB = 8;
 
-__global__ __launch_bounds__(256) void k_pass2_next(const float* __restrict__ G, int m, int64_t d, int64_t nslab,
+template <int U>
+__global__ __launch_bounds__(256) void k_pass2_next(const float* __restrict__ G, int m, int64_t d, int64_t nunit,
                                                     const double* __restrict__ coef, float* __restrict__ y,
                                                     const float* __restrict__ gn, int knext, int aligned,
                                                     double* __restrict__ part) {
+    using RU = RowUnits<U>;
+    constexpr int RB = RU::RB;
     extern __shared__ __align__(16) double sh[];
-    const int mpad = (m + 1) & ~1;  // keeps the partials 16-byte aligned
+    const int mr = (m + 4 * PASS21_RB - 1) / (4 * PASS21_RB) * (4 * PASS21_RB);  // whole rounds
     double* cl = sh;
-    double* rs = sh + mpad;    // row sums of this work-group's slabs
-    double* red = rs + mpad;   // [2][4][SLAB]
-    for (int t = threadIdx.x; t < m; t += 256) {
-        cl[t] = coef[t];
+    double* rs = sh + mr;    // row sums of this work-group's units
+    double* red = rs + mr;   // [2][4][W]
+    for (int t = threadIdx.x; t < mr; t += 256) {
+        cl[t] = t < m ? coef[t] : 0.0;
         rs[t] = 0.0;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float4 g[8], gv[8];
-    int64_t s = blockIdx.x;
-    if (s < nslab && wave < m) load_slab_row(g, G, m, s, wave, lane);
-    for (int t = 0; s < nslab; s += gridDim.x, ++t) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float4 g[RB][U], gv[U];
+    int64_t s = blockIdx.x;  // grid <= nunit
+    const float* p = RU::base(G, m, s);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) gv[u] = ld4(gn, s * SLAB + u * 256 + lane * 4, d, aligned);
-        double acc[8][4];
+    for (int r = 0; r < RB; ++r) RU::load(g[r], p, min(wave + 4 * r, m - 1), lane);
+    for (int t = 0; s < nunit; s += gridDim.x, ++t) {
+        const float* pn = s + gridDim.x < nunit ? RU::base(G, m, s + gridDim.x) : p;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.0;
-        for (int i0 = wave; i0 < m; i0 += 4 * PASS21_RB) {
+        for (int u = 0; u < U; ++u) gv[u] = ld4(gn, s * RU::W + u * 256 + lane * 4, d, aligned);
+        double acc[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.0;
+        for (int i0 = wave; i0 < mr; i0 += 4 * PASS21_RB) {
             double sv[PASS21_RB];
 #pragma unroll
             for (int r = 0; r < PASS21_RB; ++r) {
                 const int i = i0 + 4 * r;
+                float4 (&gr)[U] = g[r % RB];
                 double dv = 0.0;
-                if (i < m) {
+                // one row in flight: the branch keeps a row's work before the
+                // next row's load (unrolled without it, 200 registers spill)
+                if (RB > 1 || i < m) {
                     const double cv = cl[i];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        acc[u][0] = fma(cv, (double)g[u].x, acc[u][0]);
-                        acc[u][1] = fma(cv, (double)g[u].y, acc[u][1]);
-                        acc[u][2] = fma(cv, (double)g[u].z, acc[u][2]);
-                        acc[u][3] = fma(cv, (double)g[u].w, acc[u][3]);
+                    for (int u = 0; u < U; ++u) {
+                        acc[u][0] = fma(cv, (double)gr[u].x, acc[u][0]);
+                        acc[u][1] = fma(cv, (double)gr[u].y, acc[u][1]);
+                        acc[u][2] = fma(cv, (double)gr[u].z, acc[u][2]);
+                        acc[u][3] = fma(cv, (double)gr[u].w, acc[u][3]);
                     }
                     if (i == knext) {
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) dv = dot4d(gv[u], gv[u], dv);
+                        for (int u = 0; u < U; ++u) dv = dot4d(gv[u], gv[u], dv);
                     } else {
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) dv = dot4d(g[u], gv[u], dv);
+                        for (int u = 0; u < U; ++u) dv = dot4d(gr[u], gv[u], dv);
                     }
-                    if (i + 4 < m)
-                        load_slab_row(g, G, m, s, i + 4, lane);
-                    else if (s + gridDim.x < nslab)
-                        load_slab_row(g, G, m, s + gridDim.x, wave, lane);
+                    // formed here, not at the reduction with all eight rows kept
+                    asm volatile("" : "+v"(dv));
+                    const int il = i + 4 * RB;
+                    const bool more = RB > 1 ? il - wave - 4 * (r % RB) < mr : il < m;  // a further round of rows
+                    RU::load(gr, more ? p : pn, min(more ? il : wave + 4 * (r % RB), m - 1), lane);
                 }
                 sv[r] = dv;
             }
             int idx;
             bool writer;
             const double tot = wave_reduce_many<PASS21_RB>(sv, lane, idx, writer);
-            if (writer && i0 + 4 * idx < m) rs[i0 + 4 * idx] += tot;
+            if (writer) rs[i0 + 4 * idx] += tot;  // past m: never read
         }
-        double* rb = red + (t & 1) * 4 * SLAB;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            double* q = rb + wave * SLAB + u * 256 + lane * 4;
-            *reinterpret_cast<double2*>(q) = make_double2(acc[u][0], acc[u][1]);
-            *reinterpret_cast<double2*>(q + 2) = make_double2(acc[u][2], acc[u][3]);
-        }
-        lds_barrier();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int col = wave * 512 + h * 256 + lane * 4;
-            const int64_t j = s * SLAB + col;
-            double sum[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                sum[k] = rb[col + k] + rb[SLAB + col + k] + rb[2 * SLAB + col + k] + rb[3 * SLAB + col + k];
+        p = pn;
+        RU::reduce(red + (t & 1) * 4 * RU::W, acc, wave, lane, [&](int col, const double (&sum)[4]) {
             // y = 0 - sum (not -sum: an exact zero sum stores +0, as in k_pass2_rows)
             float4 o;
             o.x = (float)(0.0 - sum[0]);
             o.y = (float)(0.0 - sum[1]);
             o.z = (float)(0.0 - sum[2]);
             o.w = (float)(0.0 - sum[3]);
-            st4_stream(y, j, d, aligned, o);
-        }
+            st4_stream(y, s * RU::W + col, d, aligned, o);
+        });
     }
     __syncthreads();
     double* out = part + (int64_t)blockIdx.x * m;
@@ -522,22 +570,49 @@ struct PassCfg {
     static constexpr int RB2 = NV == 1 ? 8 : NV == 2 ? 4 : NV <= 4 ? 2 : NV == 5 ? 4 : 8;
 };
 
-// Pass-1 rows per work-group: the fp64 row sums of a work-group stay within
-// 80 KB of LDS (two work-groups per CU); larger m * NV splits the rows into
-// groups, each re-reading the vector chunks (NV * 4 bytes per column per extra
-// group, under 2% of the pass).
+// Pass-1 launch shape: gx work-groups on the chunks of each of ng row groups.
+// The fp64 row sums of a work-group stay within 80 KB of LDS (two work-groups
+// per CU), which sets the least ng. More row groups even out the work where the
+// chunks are few: 264 chunks (d = 269,722) on 256 work-groups leave 248 of them
+// idle for half the pass. A work-group's time is its chunks times its rows (whole
+// rounds of 4 R) plus, per chunk, the vectors' chunk and a round to fill the
+// pipeline; ng doubles while that falls by more than 2%.
 constexpr int64_t ROWSUM_LDS = 80 * 1024;
-inline Pass1Grid pass1_grid(int m, int nv, int64_t nchunk, int target) {
+inline Pass1Grid pass1_grid(int m, int nv, int64_t nchunk, int target, int round) {
     const int64_t bytes = (int64_t)m * nv * 8;
-    const int ng = (int)((bytes + ROWSUM_LDS - 1) / ROWSUM_LDS);
-    Pass1Grid pg;
-    pg.mg = (m + ng - 1) / ng;
-    pg.ng = (m + pg.mg - 1) / pg.mg;
-    int64_t gx = target / pg.ng;
-    if (gx > nchunk) gx = nchunk;
-    if (gx < 1) gx = 1;
-    pg.gx = (int)gx;
-    return pg;
+    const int ng0 = (int)((bytes + ROWSUM_LDS - 1) / ROWSUM_LDS);
+    Pass1Grid best{};
+    int64_t best_cost = 0;
+    for (int n = ng0; n <= target && (n == ng0 || n * round <= m); n *= 2) {
+        Pass1Grid pg;
+        pg.mg = (m + n - 1) / n;
+        pg.ng = (m + pg.mg - 1) / pg.mg;
+        int64_t gx = target / pg.ng;
+        if (gx > nchunk) gx = nchunk;
+        if (gx < 1) gx = 1;
+        pg.gx = (int)gx;
+        const int64_t cost = ceil_div(nchunk, gx) * (round_up(pg.mg, round) + round + nv);
+        if (n == ng0 || cost * 100 < best_cost * 98) {
+            best = pg;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Width of the units of k_pass2_rows / k_pass2_next: the widest of 2048, 1024,
+// 512 and 256 columns whose rounds over the grid are within 3% of the least.
+// Whole slabs leave most of the chip idle where they are fewer than the
+// work-groups or just more than a multiple of them.
+inline int row_unit(int64_t d) {
+    int64_t least = 0;
+    for (int u = 8; u >= 1; u /= 2) {
+        const int64_t c = ceil_div(ceil_div(d, 256 * u), PASS2_ROWS_GRID) * u;
+        if (least == 0 || c < least) least = c;
+    }
+    for (int u = 8; u > 1; u /= 2)
+        if (ceil_div(ceil_div(d, 256 * u), PASS2_ROWS_GRID) * u * 100 <= least * 103) return u;
+    return 1;
 }
 
 template <int NV>
@@ -546,7 +621,7 @@ hipError_t pass1_nv(const float* G, int m, int64_t d, int64_t nslab, const VecIn
     constexpr int U = PassCfg<NV>::U, R = PassCfg<NV>::R;
     static_assert(PassCfg<NV>::GRID <= PASS1_MAX_GRID, "partials sized for PASS1_MAX_GRID work-groups");
     const int64_t nchunk = nslab * (SLAB / (256 * U));
-    const Pass1Grid pg = pass1_grid(m, NV, nchunk, PassCfg<NV>::GRID);
+    const Pass1Grid pg = pass1_grid(m, NV, nchunk, PassCfg<NV>::GRID, 4 * R);
     const size_t lds = (size_t)pg.mg * NV * sizeof(double);
     if (lds > 65536) {
         // fp64 row sums of a row group: just above 80 KB at most. Set on every
@@ -562,19 +637,52 @@ hipError_t pass1_nv(const float* G, int m, int64_t d, int64_t nslab, const VecIn
     return hipGetLastError();
 }
 
+template <int U>
+hipError_t pass2_rows(const float* G, int m, int64_t d, const double* coef, const VecOut& vout, bool aligned,
+                      hipStream_t st) {
+    const size_t lds = (size_t)(round_up(m, 4 * RowUnits<U>::RB) + 8 * RowUnits<U>::W) * sizeof(double);
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass2_rows<U>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    const int64_t nunit = ceil_div(d, RowUnits<U>::W);
+    const int64_t grid = nunit < PASS2_ROWS_GRID ? nunit : PASS2_ROWS_GRID;
+    hipLaunchKernelGGL(k_pass2_rows<U>, dim3((unsigned)grid), dim3(256), lds, st, G, m, d, nunit, coef, vout,
+                       aligned ? 1 : 0);
+    return hipGetLastError();
+}
+
+template <int U>
+hipError_t pass2_next(const float* G, int m, int64_t d, const double* coef, float* y, const float* gn, int knext,
+                      bool aligned, double* part, Pass1Grid* grid_out, hipStream_t st) {
+    const size_t lds = (size_t)(2 * round_up(m, 4 * PASS21_RB) + 8 * RowUnits<U>::W) * sizeof(double);
+    if (lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass2_next<U>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+    }
+    const int64_t nunit = ceil_div(d, RowUnits<U>::W);
+    const int64_t grid = nunit < PASS2_ROWS_GRID ? nunit : PASS2_ROWS_GRID;
+    hipLaunchKernelGGL(k_pass2_next<U>, dim3((unsigned)grid), dim3(256), lds, st, G, m, d, nunit, coef, y, gn, knext,
+                       aligned ? 1 : 0, part);
+    grid_out->gx = (int)grid;
+    grid_out->ng = 1;
+    grid_out->mg = m;
+    return hipGetLastError();
+}
+
 template <int NV>
 hipError_t pass2_nv(const float* G, int m, int64_t d, int64_t nslab, const double* coef,
                     const VecOut& vout, bool aligned, hipStream_t st) {
     if constexpr (NV == 1) {
         if (m <= PASS2_ROWS_MAX_M) {
-            const size_t lds = (size_t)(((m + 1) & ~1) + 8 * SLAB) * sizeof(double);
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass2_rows),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            const int64_t grid = nslab < PASS2_ROWS_GRID ? nslab : PASS2_ROWS_GRID;
-            hipLaunchKernelGGL(k_pass2_rows, dim3((unsigned)grid), dim3(256), lds, st, G, m, d, nslab, coef, vout,
-                               aligned ? 1 : 0);
-            return hipGetLastError();
+            switch (row_unit(d)) {
+                case 8: return pass2_rows<8>(G, m, d, coef, vout, aligned, st);
+                case 4: return pass2_rows<4>(G, m, d, coef, vout, aligned, st);
+                case 2: return pass2_rows<2>(G, m, d, coef, vout, aligned, st);
+                default: return pass2_rows<1>(G, m, d, coef, vout, aligned, st);
+            }
         }
     }
     constexpr int U = PassCfg<NV>::U2, RB = PassCfg<NV>::RB2;
@@ -649,17 +757,12 @@ hipError_t launch_pass2_next(const float* G, int m, int64_t d, int64_t nslab, co
                              const float* gn, int knext, bool aligned, double* part, Pass1Grid* grid_out,
                              hipStream_t st) {
     if (m > PASS21_MAX_M) return hipErrorInvalidValue;
-    const size_t lds = (size_t)(2 * ((m + 1) & ~1) + 8 * SLAB) * sizeof(double);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_pass2_next),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    const int64_t grid = nslab < PASS2_ROWS_GRID ? nslab : PASS2_ROWS_GRID;
-    hipLaunchKernelGGL(k_pass2_next, dim3((unsigned)grid), dim3(256), lds, st, G, m, d, nslab, coef, y, gn, knext,
-                       aligned ? 1 : 0, part);
-    grid_out->gx = (int)grid;
-    grid_out->ng = 1;
-    grid_out->mg = m;
-    return hipGetLastError();
+    switch (row_unit(d)) {
+        case 8: return pass2_next<8>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);
+        case 4: return pass2_next<4>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);
+        case 2: return pass2_next<2>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);
+        default: return pass2_next<1>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);
+    }
 }
 
 hipError_t launch_reduce_partials(const double* part, const Pass1Grid& pg, int m, int nv, double* p,

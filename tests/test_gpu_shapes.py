@@ -119,3 +119,30 @@ def test_fast_obs_update_without_and_with_w(dev, m, B, nb):
     ref = ostatic.obs_update(G.numpy(), wl.lam, B, theta.numpy(), mask.numpy())
     assert rel_l2(d1, ref) < 4e-6
     assert rel_l2(d2, ref) < 4e-6
+
+
+# units of 2048, 1024, 512 and 256 columns in the one-vector passes: fewer units
+# than work-groups, just over a multiple of them, a ragged last unit; m below and
+# at the rows in flight, and rows that no round of the pass divides; one to many
+# row groups in pass 1
+@pytest.mark.parametrize("d,m", [(1, 1), (255, 3), (2049, 33), (66_001, 31), (131_073, 65), (269_722, 40),
+                                 (525_000, 17), (530_000, 5), (1_050_000, 9)])
+def test_single_vector_units(dev, d, m):
+    from paper_2107_03356_amd import Window
+    say("single-vector units d =", d, "m =", m)
+    gs = _stream(d, m, 1e-3, seed=d)
+    G0 = gs.window()
+    win = Window(d, m, 1e-3, G0=G0.to(dev), device=dev)
+    orc = WindowOracle(d, m, 1e-3, G0=G0.numpy())
+    x = gs.queries(0, 1)
+    assert rel_l2(win.ihvp(x.to(dev)).cpu().numpy()[0], orc.ihvp(x.numpy())[0]) < F32_TOL
+    for t in range(2):
+        g = gs.step_row(t)
+        y = win.replace(g.to(dev)).cpu().numpy()
+        assert rel_l2(y, orc.slide(g.numpy())) < F32_TOL
+    # a known sequence, in both directions of the fused pass
+    Gn = torch.stack([gs.step_row(2 + t) for t in range(3)])
+    Yn = win.replace_seq(Gn.to(dev)).cpu().numpy()
+    for t in range(3):
+        assert rel_l2(Yn[t], orc.slide(Gn[t].numpy())) < F32_TOL
+    assert win.status() == 0
