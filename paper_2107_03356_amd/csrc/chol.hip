@@ -12,68 +12,11 @@
 // O(m^2) slot replacement updates A^-1 in place between refactors; and the
 // coefficient kernel applies it. A is padded to a multiple of 64 with an
 // identity block so no kernel needs edge handling.
-//
-// Dense 64 x 64 x 64 tile products (k_lauum) run on fp64 MFMA
-// (v_mfma_f64_16x16x4f64): 4 waves, each a 32 x 32 quadrant of 2 x 2 16x16
-// tiles, operands from LDS. They are written as C[r][c] = sum_k a[r][k] *
-// b[c][k]; a tile that enters as b[k][c] is transposed while it is staged.
 #include "internal.h"
 #include "tile_util.h"
 
 namespace mfac {
 namespace {
-
-constexpr int P = 68;  // LDS pitch of a 64 x 64 fp64 tile
-
-__device__ __forceinline__ void stage_tile_t(double (*S)[P], const double* __restrict__ src, int64_t ld) {
-    for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-        const int r = e >> 6, c = e & 63;
-        S[c][r] = src[(int64_t)r * ld + c];
-    }
-}
-
-__device__ __forceinline__ void zero_acc(v4d (&acc)[2][2]) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = v4d{0.0, 0.0, 0.0, 0.0};
-}
-
-// acc += a * b^T over k in [0, 64) for this wave's quadrant (256 threads).
-__device__ __forceinline__ void mma_nt(const double (*a)[P], const double (*b)[P], v4d (&acc)[2][2]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int rl = lane & 15, kl = lane >> 4;
-#pragma unroll 4
-    for (int kk = 0; kk < 16; ++kk) {
-        double av[2], bv[2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            av[s] = a[wr * 32 + s * 16 + rl][kk * 4 + kl];
-            bv[s] = b[wc * 32 + s * 16 + rl][kk * 4 + kl];
-        }
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int y = 0; y < 2; ++y)
-                acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x], bv[y], acc[x][y], 0, 0, 0);
-    }
-}
-
-// Visit this thread's accumulator entries: f(row, col, value). In the fp64
-// 16x16x4 MFMA result, lane l register r holds row (l/16) + 4r, column l%16.
-template <typename F>
-__device__ __forceinline__ void for_acc(v4d (&acc)[2][2], F f) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int rl = lane & 15, kl = lane >> 4;
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) f(wr * 32 + x * 16 + kl + 4 * r, wc * 32 + y * 16 + rl, acc[x][y][r]);
-}
 
 // ------------------------------------------------------------------ assemble
 __global__ __launch_bounds__(256) void k_assemble(double* __restrict__ K, int m,
@@ -341,26 +284,94 @@ __global__ __launch_bounds__(256) void k_zero_superdiag(R* __restrict__ Linv, in
 }
 
 // ------------------------------------------------------------------ explicit inverse
-// Ainv = (A)^-1 = Linv^T Linv, tile (I, J) = sum_{K >= max(I,J)} Linv[K,I]^T Linv[K,J].
-// grid (T*T, nbatch).
-__global__ __launch_bounds__(256) void k_lauum(const double* __restrict__ Linv, double* __restrict__ Ainv, int mp,
+// Ainv = (A)^-1 = Linv^T Linv: 64 x 64 tile (I, J), I >= J, is the sum over k >=
+// 64 I of Linv[k, I]^T Linv[k, J], written to both triangles. One matrix has few
+// tiles (136 at m = 1024) and the longest walks all of k, so a work-group is two
+// groups of four waves (32 x 32 quadrants), each with half of the k range in
+// 16-deep chunks double-buffered in LDS with the next chunk's loads in flight;
+// the halves meet in LDS. (Every tile of the full square, 64-deep stages loaded
+// between the products: 140 us at m = 1024; this: 43 us.) Grid (T (T + 1) / 2, nbatch).
+constexpr int LK = 16, LP = 80;  // chunk depth; pitch: rows k .. k + 3 of a 16-column read on disjoint banks
+__global__ __launch_bounds__(512) void k_lauum(const double* __restrict__ Linv, double* __restrict__ Ainv, int mp,
                                                int64_t bstride) {
-    __shared__ double Sa[64][P];
-    __shared__ double Sb[64][P];
-    const int T = mp / 64;
-    const int I = blockIdx.x / T, J = blockIdx.x % T;
+    __shared__ __align__(16) double Sa[2][2][LK][LP], Sb[2][2][LK][LP];  // [group][buffer]
+    int I = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+    while ((I + 1) * (I + 2) / 2 <= (int)blockIdx.x) ++I;
+    while (I * (I + 1) / 2 > (int)blockIdx.x) --I;
+    const int J = blockIdx.x - I * (I + 1) / 2;
+    const int g = threadIdx.x >> 8, t = threadIdx.x & 255;
+    const int lane = t & 63, wave = t >> 6;
+    const int wr = wave >> 1, wc = wave & 1, rl = lane & 15, kl = lane >> 4;
     const double* Lb = Linv + (int64_t)blockIdx.y * bstride;
+    const int nc = (mp - I * 64) / (2 * LK);  // chunks per group
+    // thread t of a group: row t / 16 of the chunk, columns 4 (t % 16) .. +3
+    const int sr = t >> 4, sc = (t & 15) * 4;
+    const double* src = Lb + (int64_t)(I * 64 + g * nc * LK + sr) * mp + sc;
+    double2 a0, a1, b0, b1;
+    auto load = [&](int c) {
+        const double* q = src + (int64_t)c * LK * mp;
+        a0 = *reinterpret_cast<const double2*>(q + I * 64);
+        a1 = *reinterpret_cast<const double2*>(q + I * 64 + 2);
+        b0 = *reinterpret_cast<const double2*>(q + J * 64);
+        b1 = *reinterpret_cast<const double2*>(q + J * 64 + 2);
+    };
+    auto store = [&](int buf) {
+        *reinterpret_cast<double2*>(&Sa[g][buf][sr][sc]) = a0;
+        *reinterpret_cast<double2*>(&Sa[g][buf][sr][sc + 2]) = a1;
+        *reinterpret_cast<double2*>(&Sb[g][buf][sr][sc]) = b0;
+        *reinterpret_cast<double2*>(&Sb[g][buf][sr][sc + 2]) = b1;
+    };
     v4d acc[2][2];
-    zero_acc(acc);
-    for (int K = (I > J ? I : J); K < T; ++K) {
-        stage_tile_t(Sa, Lb + (int64_t)K * 64 * mp + I * 64, mp);
-        stage_tile_t(Sb, Lb + (int64_t)K * 64 * mp + J * 64, mp);
-        __syncthreads();
-        mma_nt(Sa, Sb, acc);
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = v4d{0.0, 0.0, 0.0, 0.0};
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int c = 0; c < nc; ++c) {
+        const int buf = c & 1;
+        if (c + 1 < nc) load(c + 1);
+#pragma unroll
+        for (int kk = 0; kk < LK / 4; ++kk) {
+            double av[2], bv[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                av[s] = Sa[g][buf][kk * 4 + kl][wr * 32 + s * 16 + rl];
+                bv[s] = Sb[g][buf][kk * 4 + kl][wc * 32 + s * 16 + rl];
+            }
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x], bv[y], acc[x][y], 0, 0, 0);
+        }
+        if (c + 1 < nc) store(buf ^ 1);
         __syncthreads();
     }
-    double* C = Ainv + (int64_t)blockIdx.y * bstride + (int64_t)I * 64 * mp + J * 64;
-    for_acc(acc, [&](int row, int col, double v) { C[(int64_t)row * mp + col] = v; });
+    // group 1's tile, then the sum, through LDS (over the chunks' buffers)
+    double (*S)[65] = reinterpret_cast<double (*)[65]>(&Sa[0][0][0][0]);
+    static_assert(64 * 65 <= 2 * 2 * LK * LP, "the tile fits the chunk buffers");
+    for (int pass = 1; pass >= 0; --pass) {
+        if (g == pass) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        double& e = S[wr * 32 + x * 16 + mfma64_row(lane, r)][wc * 32 + y * 16 + rl];
+                        e = pass == 1 ? acc[x][y][r] : acc[x][y][r] + e;
+                    }
+        }
+        __syncthreads();
+    }
+    double* C = Ainv + (int64_t)blockIdx.y * bstride;
+    for (int e = threadIdx.x; e < 4096; e += 512) {
+        const int r = e >> 6, c = e & 63;
+        C[(int64_t)(I * 64 + r) * mp + J * 64 + c] = S[r][c];
+        if (I != J) C[(int64_t)(J * 64 + r) * mp + I * 64 + c] = S[c][r];
+    }
 }
 
 __device__ __forceinline__ double wave_sum_d(double x) {
@@ -558,7 +569,7 @@ template hipError_t launch_zero_superdiag<float>(float*, int, int, int64_t, hipS
 
 hipError_t launch_lauum(const double* Linv, double* Ainv, int mp, int nbatch, int64_t bstride, hipStream_t st) {
     const int T = mp / 64;
-    hipLaunchKernelGGL(k_lauum, dim3(T * T, nbatch), dim3(256), 0, st, Linv, Ainv, mp, bstride);
+    hipLaunchKernelGGL(k_lauum, dim3(T * (T + 1) / 2, nbatch), dim3(512), 0, st, Linv, Ainv, mp, bstride);
     return hipGetLastError();
 }
 
