@@ -40,6 +40,64 @@ __device__ __forceinline__ void tile_of(int idx, int& ti, int& tj) {
     tj = idx - t * (t + 1) / 2;
 }
 
+// Wave -> 32 x 64 piece of a 128 x 128 tile (fp64 kernels). Waves w and w + 4
+// share a SIMD (round-robin placement): the pieces of a diagonal tile hold 0, 0,
+// 3, 3, 7, 7, 8 and 8 parts of 16 x 16 that reach the diagonal, paired here as
+// 8 + 0, 8 + 0, 7 + 3, 7 + 3.
+__device__ __forceinline__ void lower_piece(int wave, int& wr, int& wc) {
+    // (2,0) (3,0) (1,0) (3,1) | (0,1) (1,1) (0,0) (2,1), as 2 wr + wc
+    const int code = (0x50317264 >> (4 * wave)) & 15;
+    wr = code >> 1;
+    wc = code & 1;
+}
+
+// The 2 x 4 parts (bit 4 x + y) of a diagonal tile's piece that reach the diagonal.
+__device__ __forceinline__ unsigned lower_parts(int wr, int wc) {
+    unsigned on = 0;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+            if (wr * 32 + x * 16 >= wc * 64 + y * 16) on |= 1u << (4 * x + y);
+    return on;
+}
+
+// acc += A B^T over one KB-column chunk of fp32 operands, in fp64, for the parts
+// in `on` (the same in every lane; ALL: every part). The caller keeps the two
+// forms in loops of their own: one loop with both spills accumulators.
+template <bool ALL>
+__device__ __forceinline__ void gram_chunk(const float (*Ab)[PITCH], const float (*Bb)[PITCH], int wr, int wc, int lane,
+                                           unsigned on, v4d (&acc)[2][4]) {
+    const int rl = lane & 15, kl = lane >> 4;
+    if constexpr (ALL) {
+#pragma unroll
+        for (int kk = 0; kk < KB / 4; ++kk) {
+            double av[2], bv[4];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) av[x] = (double)Ab[wr * 32 + x * 16 + rl][kk * 4 + kl];
+#pragma unroll
+            for (int y = 0; y < 4; ++y) bv[y] = (double)Bb[wc * 64 + y * 16 + rl][kk * 4 + kl];
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x], bv[y], acc[x][y], 0, 0, 0);
+        }
+    } else {
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                if ((on >> (4 * x + y)) & 1u) {
+#pragma unroll
+                    for (int kk = 0; kk < KB / 4; ++kk)
+                        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            (double)Ab[wr * 32 + x * 16 + rl][kk * 4 + kl],
+                            (double)Bb[wc * 64 + y * 16 + rl][kk * 4 + kl], acc[x][y], 0, 0, 0);
+                }
+    }
+}
+
 // Window Gram partials. Grid (ntiles, nsplit): work-group (t, s) computes the
 // 128 x 128 lower tile t of K over slabs [s*sps, min(nslab, (s+1)*sps)). Eight
 // waves, each owning a 32 x 64 piece as 2 x 4 fp64 MFMA tiles (two waves per
@@ -58,11 +116,13 @@ __global__ __launch_bounds__(512, 4) void k_gram_window(const float* __restrict_
     int ti, tj;
     tile_of(blockIdx.x, ti, tj);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;  // rows wr*32, columns wc*64
+    int wr, wc;  // rows wr*32, columns wc*64
+    lower_piece(wave, wr, wc);
     const int rl = lane & 15, kl = lane >> 4;
-    // in a diagonal tile, waves whose piece lies wholly above the diagonal only
-    // stage operands (the reduction reads the lower triangle of such tiles)
-    const bool upper_wave = ti == tj && wr * 32 + 31 < wc * 64;
+    // in a diagonal tile only the 16 x 16 parts that reach the diagonal are
+    // formed (the reduction reads the lower triangle of such tiles); the waves
+    // without any only stage operands
+    const unsigned on = ti == tj ? lower_parts(wr, wc) : 255u;
     const int64_t s0 = (int64_t)blockIdx.y * sps;
     const int64_t s1 = min(s0 + sps, nslab);
 
@@ -103,38 +163,30 @@ __global__ __launch_bounds__(512, 4) void k_gram_window(const float* __restrict_
         MFAC_GW_STORE(0)
         __syncthreads();
     }
-    int buf = 0;
-    for (int64_t s = s0; s < s1; ++s) {
-        for (int c = 0; c < NCH; ++c) {
-            // next chunk: the following columns of this slab, or the next slab's first
-            const bool more = c + 1 < NCH || s + 1 < s1;
-            const int64_t sn = c + 1 < NCH ? s : s + 1;
-            const int kn = c + 1 < NCH ? (c + 1) * KB : 0;
-            if (more) MFAC_GW_LOAD(sn, kn)
-            float (*Ab)[PITCH] = As[buf];
-            float (*Bb)[PITCH] = Bs[buf];
-            if (!upper_wave) {
-#pragma unroll
-                for (int kk = 0; kk < KB / 4; ++kk) {
-                    double av[2], bv[4];
-#pragma unroll
-                    for (int x = 0; x < 2; ++x) av[x] = (double)Ab[wr * 32 + x * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                    for (int y = 0; y < 4; ++y) bv[y] = (double)Bb[wc * 64 + y * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                    for (int x = 0; x < 2; ++x)
-#pragma unroll
-                        for (int y = 0; y < 4; ++y)
-                            accd[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x], bv[y], accd[x][y], 0, 0, 0);
-                }
+    auto walk = [&](auto all) {
+        int buf = 0;
+        for (int64_t s = s0; s < s1; ++s) {
+            for (int c = 0; c < NCH; ++c) {
+                // next chunk: the following columns of this slab, or the next slab's first
+                const bool more = c + 1 < NCH || s + 1 < s1;
+                const int64_t sn = c + 1 < NCH ? s : s + 1;
+                const int kn = c + 1 < NCH ? (c + 1) * KB : 0;
+                if (more) MFAC_GW_LOAD(sn, kn)
+                float (*Ab)[PITCH] = As[buf];
+                float (*Bb)[PITCH] = Bs[buf];
+                gram_chunk<decltype(all)::value>(Ab, Bb, wr, wc, lane, on, accd);
+                if (more) MFAC_GW_STORE(buf ^ 1)
+                __syncthreads();
+                buf ^= 1;
             }
-            if (more) MFAC_GW_STORE(buf ^ 1)
-            __syncthreads();
-            buf ^= 1;
         }
-    }
+    };
+    if (ti == tj)
+        walk(std::false_type{});
+    else
+        walk(std::true_type{});
 
-    if (upper_wave) return;
+    if (!on) return;
     double* out = part + ((int64_t)blockIdx.y * ntiles + blockIdx.x) * (WT * WT);
 #pragma unroll
     for (int x = 0; x < 2; ++x)
@@ -223,12 +275,13 @@ __global__ __launch_bounds__(512, 4) void k_gram_blocks(const float* __restrict_
     int ti, tj;
     tile_of(tile, ti, tj);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;  // rows wr*32, columns wc*64
+    int wr, wc;  // rows wr*32, columns wc*64
+    lower_piece(wave, wr, wc);
     const int rl = lane & 15, kl = lane >> 4;
     const bool diag_tile = ti == tj;
     // in a diagonal tile the part above the diagonal is never read (the
-    // factorization uses the lower triangle): waves wholly above it only stage
-    const bool upper_wave = diag_tile && wr * 32 + 31 < wc * 64;
+    // factorization uses the lower triangle): see k_gram_window
+    const unsigned on = diag_tile ? lower_parts(wr, wc) : 255u;
     const int cbeg = sp * kcols;
     const int ncols = (B - cbeg) < kcols ? (B - cbeg) : kcols;
     const float* base = G + (int64_t)(b0 + bl) * B + cbeg;
@@ -274,32 +327,22 @@ __global__ __launch_bounds__(512, 4) void k_gram_blocks(const float* __restrict_
     MFAC_GB_LOAD(0)
     MFAC_GB_STORE(0, 0)
     __syncthreads();
-    for (int c = 0; c < nchunk; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < nchunk) MFAC_GB_LOAD((c + 1) * KB)
-        float (*Ab)[PITCH] = As[buf];
-        float (*Bb)[PITCH] = diag_tile ? As[buf] : Bs[buf];
-        if (!upper_wave) {
-#pragma unroll
-            for (int kk = 0; kk < KB / 4; ++kk) {
-                double av[2], bv[4];
-#pragma unroll
-                for (int x = 0; x < 2; ++x) av[x] = (double)Ab[wr * 32 + x * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                for (int y = 0; y < 4; ++y) bv[y] = (double)Bb[wc * 64 + y * 16 + rl][kk * 4 + kl];
-#pragma unroll
-                for (int x = 0; x < 2; ++x)
-#pragma unroll
-                    for (int y = 0; y < 4; ++y)
-                        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[x], bv[y], acc[x][y], 0, 0, 0);
-            }
+    auto walk = [&](auto all) {
+        for (int c = 0; c < nchunk; ++c) {
+            const int buf = c & 1;
+            if (c + 1 < nchunk) MFAC_GB_LOAD((c + 1) * KB)
+            gram_chunk<decltype(all)::value>(As[buf], diag_tile ? As[buf] : Bs[buf], wr, wc, lane, on, acc);
+            if (c + 1 < nchunk) MFAC_GB_STORE(buf ^ 1, (c + 1) * KB)
+            __syncthreads();
         }
-        if (c + 1 < nchunk) MFAC_GB_STORE(buf ^ 1, (c + 1) * KB)
-        __syncthreads();
-    }
+    };
+    if (diag_tile)
+        walk(std::false_type{});
+    else
+        walk(std::true_type{});
 #undef MFAC_GB_LOAD
 #undef MFAC_GB_STORE
-    if (upper_wave) return;
+    if (!on) return;
     if (nsplit > 1) {
         double* out = part + ((int64_t)bl * nsplit + sp) * ntiles * (GT * GT) + (int64_t)tile * (GT * GT);
 #pragma unroll
