@@ -13,9 +13,9 @@
 // in flight during the current chunk's MFMAs.
 //
 // Keep-mask (Section 4.1, OBD saliency, global over all blocks): fp64 scores,
-// then an 8-pass radix selection of the keep-th largest key (8-bit digits of
-// the IEEE bit pattern, which orders non-negative doubles), then a mask pass
-// that ranks exact ties by index with a deterministic chunked scan.
+// then a radix selection of the keep-th largest key (digits of the IEEE bit
+// pattern, which orders non-negative doubles), then a mask pass that ranks
+// exact ties by index with a deterministic chunked scan.
 #include <type_traits>
 
 #include "internal.h"
@@ -326,96 +326,183 @@ __device__ __forceinline__ unsigned long long key_of(double x) {
     return (unsigned long long)__double_as_longlong(x);
 }
 
-// state: [0] prefix, [1] mask, [2] remaining rank (1-based) among keys matching the prefix
-__global__ void k_select_init(unsigned long long* state, unsigned int* hist, int64_t keep) {
-    if (threadIdx.x == 0) {
-        state[0] = 0ull;
-        state[1] = 0ull;
-        state[2] = (unsigned long long)keep;
+// Selection of the keep-th largest key: radix passes over 11-bit digits from the
+// top (11 x 5 + 9 bits), a histogram each. Launch-bound at small d (a pass reads
+// d doubles: 5 us at 4M), so a pass is one launch: every work-group of pass p
+// first picks the digit of pass p - 1 from that pass's finished histogram, the
+// same way (work-group 0 notes it for the next pass), then counts its own. (8-bit
+// digits, with a one-work-group pick after every pass, one thread walking the
+// 256 counts: 17 launches, 96 us at d = 1M; this: 8 launches, 40 us.)
+// state: [0] the selected key, [2] how many keys equal to it are kept, [3]
+// whether that is all of them; pass p starts from prefix state[4 + 2 p] and
+// 1-based rank state[5 + 2 p] among the keys with that prefix.
+constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS, SEL_PASSES = 6;
+__host__ __device__ constexpr int sel_shift(int pass) { return pass < 5 ? 64 - SEL_BITS * (pass + 1) : 0; }
+
+__device__ __forceinline__ unsigned int wave_scan_u32(unsigned int x, int lane) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
     }
-    hist[threadIdx.x] = 0u;
+    return x;
+}
+
+// Inclusive sum over the 256 threads of a work-group; sh: 4 words.
+__device__ __forceinline__ unsigned int block_scan_u32(unsigned int x, unsigned int* sh) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    x = wave_scan_u32(x, lane);
+    __syncthreads();
+    if (lane == 63) sh[wave] = x;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) x += sh[w];
+    return x;
+}
+
+struct Picked {
+    unsigned long long prefix, rem;
+    unsigned int count;  // keys in the picked bin
+};
+
+// The digit holding rank rem, counting from the top digit down (256 threads).
+__device__ __forceinline__ Picked select_pick(const unsigned int* __restrict__ hist, int pass,
+                                              unsigned long long prefix, unsigned long long rem, unsigned int* sh,
+                                              Picked* shp) {
+    constexpr int PER = SEL_BINS / 256;
+    unsigned int h[PER], sum = 0;
+    const int top = SEL_BINS - 1 - (int)threadIdx.x * PER;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        h[q] = hist[pass * SEL_BINS + top - q];
+        sum += h[q];
+    }
+    const unsigned int incl = block_scan_u32(sum, sh);
+    unsigned long long above = incl - sum;
+    if (above < rem && incl >= rem) {  // one thread
+        bool found = false;
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (!found) {
+                if (above + h[q] >= rem) {
+                    found = true;
+                    shp->prefix = prefix | ((unsigned long long)(top - q) << sel_shift(pass));
+                    shp->rem = rem - above;
+                    shp->count = h[q];
+                } else {
+                    above += h[q];
+                }
+            }
+    }
+    __syncthreads();
+    return *shp;
+}
+
+// clears the histograms (and count, or nullptr); grid SEL_PASSES * SEL_BINS / 256
+__global__ __launch_bounds__(256) void k_select_init(unsigned long long* state, unsigned int* hist, int64_t keep,
+                                                     unsigned int* count) {
+    hist[blockIdx.x * 256 + threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        state[4] = 0ull;
+        state[5] = (unsigned long long)keep;
+        if (count) *count = 0u;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_select_hist(const double* __restrict__ s, int64_t d,
-                                                     const unsigned long long* __restrict__ state, int shift,
+                                                     unsigned long long* __restrict__ state, int pass,
                                                      unsigned int* __restrict__ hist) {
-    __shared__ unsigned int h[256];
-    h[threadIdx.x] = 0u;
-    __syncthreads();
-    const unsigned long long prefix = state[0], mask = state[1];
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (; i < d; i += stride) {
-        const unsigned long long k = key_of(s[i]);
-        if ((k & mask) == prefix) atomicAdd(&h[(unsigned)((k >> shift) & 255ull)], 1u);
+    __shared__ unsigned int h[SEL_BINS], sh[4];
+    __shared__ Picked shp;
+    const int lane = threadIdx.x & 63;
+    for (int t = threadIdx.x; t < SEL_BINS; t += 256) h[t] = 0u;
+    unsigned long long prefix = state[4 + 2 * (pass > 0 ? pass - 1 : 0)];
+    if (pass > 0) {
+        const Picked pk = select_pick(hist, pass - 1, prefix, state[5 + 2 * (pass - 1)], sh, &shp);
+        prefix = pk.prefix;
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            state[4 + 2 * pass] = pk.prefix;
+            state[5 + 2 * pass] = pk.rem;
+        }
     }
     __syncthreads();
-    const unsigned int c = h[threadIdx.x];
-    if (c) atomicAdd(&hist[threadIdx.x], c);
+    const int shift = sel_shift(pass), high = pass > 0 ? sel_shift(pass - 1) : 64;
+    const unsigned int dmask = pass < 5 ? SEL_BINS - 1 : (1u << sel_shift(4)) - 1;
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    // whole waves stay in the loop (the counting below is across the wave)
+    for (int64_t base = (int64_t)blockIdx.x * 256; base < d; base += 4 * stride) {
+        const int64_t i = i0 + (base - (int64_t)blockIdx.x * 256);
+        unsigned long long k[4];
+        bool in[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            in[q] = i + q * stride < d;
+            k[q] = in[q] ? key_of(s[i + q * stride]) : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool use = in[q] && (high == 64 || ((k[q] ^ prefix) >> high) == 0);
+            const unsigned int dg = (unsigned int)(k[q] >> shift) & dmask;
+            // the lanes that share the first counted lane's digit add once: the
+            // top digits of most keys are the same
+            const unsigned long long act = __ballot(use);
+            if (act) {
+                const int first = __ffsll((unsigned long long)act) - 1;
+                const unsigned int d0 = __shfl(dg, first, 64);
+                const unsigned long long same = __ballot(use && dg == d0);
+                if (lane == first)
+                    atomicAdd(&h[d0], (unsigned int)__popcll(same));
+                else if (use && dg != d0)
+                    atomicAdd(&h[dg], 1u);
+            }
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < SEL_BINS; t += 256)
+        if (h[t]) atomicAdd(&hist[pass * SEL_BINS + t], h[t]);
 }
 
-// Pick the digit holding the remaining rank, counting from the top digit down.
-__global__ void k_select_pick(unsigned long long* state, unsigned int* hist, int shift) {
-    __shared__ unsigned int h[256];
-    h[threadIdx.x] = hist[threadIdx.x];
-    __syncthreads();
-    hist[threadIdx.x] = 0u;  // ready for the next pass
+// the last pass's digit: the selected key
+__global__ __launch_bounds__(256) void k_select_last(unsigned long long* state, const unsigned int* __restrict__ hist) {
+    __shared__ unsigned int sh[4];
+    __shared__ Picked shp;
+    constexpr int L = SEL_PASSES - 1;
+    const Picked pk = select_pick(hist, L, state[4 + 2 * L], state[5 + 2 * L], sh, &shp);
     if (threadIdx.x == 0) {
-        unsigned long long rem = state[2];
-        unsigned long long above = 0;
-        int dsel = 0;
-        for (int dg = 255; dg >= 0; --dg) {
-            if (above + h[dg] >= rem) {
-                dsel = dg;
-                break;
-            }
-            above += h[dg];
-        }
-        state[0] |= ((unsigned long long)dsel) << shift;
-        state[1] |= 255ull << shift;
-        state[2] = rem - above;
+        state[0] = pk.prefix;
+        state[2] = pk.rem;
+        state[3] = pk.rem == pk.count ? 1ull : 0ull;
     }
 }
 
 constexpr int CHUNK = 1024;  // elements per mask chunk (256 threads x 4)
 
+// Per-chunk counts of the keys equal to the selected one, needed only where some
+// of them are kept and some not.
 __global__ __launch_bounds__(256) void k_tie_count(const double* __restrict__ s, int64_t d,
                                                    const unsigned long long* __restrict__ state,
                                                    unsigned int* __restrict__ cnt) {
-    __shared__ unsigned int red[256];
+    if (state[3]) return;
+    __shared__ unsigned int sh[4];
     const unsigned long long T = state[0];
     const int64_t base = (int64_t)blockIdx.x * CHUNK + threadIdx.x * 4;
     unsigned int c = 0;
     for (int q = 0; q < 4; ++q)
         if (base + q < d && key_of(s[base + q]) == T) ++c;
-    red[threadIdx.x] = c;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) cnt[blockIdx.x] = red[0];
+    c = block_scan_u32(c, sh);
+    if (threadIdx.x == 255) cnt[blockIdx.x] = c;
 }
 
 // exclusive scan of the per-chunk tie counts, in place (one work-group)
-__global__ __launch_bounds__(256) void k_tie_scan(unsigned int* __restrict__ cnt, int n) {
-    __shared__ unsigned int tot[256];
+__global__ __launch_bounds__(256) void k_tie_scan(unsigned int* __restrict__ cnt, int n,
+                                                  const unsigned long long* __restrict__ state) {
+    if (state[3]) return;
+    __shared__ unsigned int sh[4];
     const int per = (n + 255) / 256;
     const int lo = threadIdx.x * per;
     unsigned int s = 0;
     for (int i = lo; i < lo + per && i < n; ++i) s += cnt[i];
-    tot[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned int run = 0;
-        for (int k = 0; k < 256; ++k) {
-            const unsigned int v = tot[k];
-            tot[k] = run;
-            run += v;
-        }
-    }
-    __syncthreads();
-    unsigned int run = tot[threadIdx.x];
+    unsigned int run = block_scan_u32(s, sh) - s;
     for (int i = lo; i < lo + per && i < n; ++i) {
         const unsigned int v = cnt[i];
         cnt[i] = run;
@@ -427,9 +514,10 @@ __global__ __launch_bounds__(256) void k_mask(const double* __restrict__ s, int6
                                               const unsigned long long* __restrict__ state,
                                               const unsigned int* __restrict__ chunk_prefix,
                                               uint8_t* __restrict__ mask) {
-    __shared__ unsigned int pre[256];
+    __shared__ unsigned int sh[4];
     const unsigned long long T = state[0];
     const unsigned long long need = state[2];  // ties kept, in index order
+    const bool all = state[3] != 0;
     const int64_t base = (int64_t)blockIdx.x * CHUNK + threadIdx.x * 4;
     unsigned long long k[4];
     unsigned int c = 0;
@@ -437,25 +525,15 @@ __global__ __launch_bounds__(256) void k_mask(const double* __restrict__ s, int6
         k[q] = (base + q < d) ? key_of(s[base + q]) : 0ull;
         if (base + q < d && k[q] == T) ++c;
     }
-    pre[threadIdx.x] = c;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned int run = 0;
-        for (int t = 0; t < 256; ++t) {
-            const unsigned int v = pre[t];
-            pre[t] = run;
-            run += v;
-        }
-    }
-    __syncthreads();
-    unsigned long long rank = (unsigned long long)chunk_prefix[blockIdx.x] + pre[threadIdx.x];
+    unsigned long long rank = 0;
+    if (!all) rank = (unsigned long long)chunk_prefix[blockIdx.x] + (block_scan_u32(c, sh) - c);
     for (int q = 0; q < 4; ++q) {
         if (base + q >= d) break;
         uint8_t out;
         if (k[q] > T) {
             out = 1;
         } else if (k[q] == T) {
-            out = rank < need ? 1 : 0;
+            out = all || rank < need ? 1 : 0;
             ++rank;
         } else {
             out = 0;
@@ -814,9 +892,9 @@ __global__ __launch_bounds__(256) void k_br_final(const float* __restrict__ G, i
 // Then [F_b^-1]_jj = (1 - g.x) / lambda and its score. One work-group of 8
 // waves per band coordinate, persistent over the band list; every sum has a
 // fixed order, so the results do not depend on the schedule. LDS: x, r, z (m
-// doubles each) and a chunk of G_b^T x. Entries below BR_SLOTS were refined
-// by the wide kernels: the converged ones are skipped, the others resume from
-// their x.
+// doubles each) and a chunk of G_b^T x. With bw.x set, entries below BR_SLOTS were
+// refined by the wide kernels: the converged ones are skipped, the others resume
+// from their x.
 __global__ __launch_bounds__(BAND_THREADS) void k_band_refine(const float* __restrict__ G, int m, int64_t d, int B,
                                                               const float* __restrict__ L32, int mp, int64_t lstride,
                                                               const unsigned int* __restrict__ count,
@@ -835,7 +913,7 @@ __global__ __launch_bounds__(BAND_THREADS) void k_band_refine(const float* __res
     const unsigned int n = *count;
     const double mu = (double)m * lam;
     for (unsigned int c = blockIdx.x; c < n; c += gridDim.x) {
-        const bool resume = c < (unsigned int)BR_SLOTS;
+        const bool resume = bw.x && c < (unsigned int)BR_SLOTS;
         if (resume && band_converged(bw, (int)c, BR_ITERS)) continue;
         const int64_t j = list[c];
         const int64_t b = j / B;
@@ -984,11 +1062,6 @@ __global__ __launch_bounds__(BAND_THREADS) void k_band_refine(const float* __res
     }
 }
 
-__global__ void k_fill_u32(unsigned int* __restrict__ p, int n, unsigned int v) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 __global__ void k_fill_u8(uint8_t* __restrict__ p, int64_t n, uint8_t v) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) p[i] = v;
@@ -1032,36 +1105,33 @@ hipError_t launch_scores(const float* theta, const double* diag, int64_t d, doub
 
 int64_t select_scratch_bytes(int64_t d) {
     const int64_t nchunk = ceil_div(d, CHUNK);
-    return 256 * 4 + 4 * 8 + round_up(nchunk * 4, 256) + 256;
+    return SEL_PASSES * SEL_BINS * 4 + 256 + round_up(nchunk * 4, 256);
 }
 
 SelectScratch select_scratch_carve(void* base, int64_t d) {
     SelectScratch s;
     char* p = (char*)base;
     s.hist = (unsigned int*)p;
-    s.state = (unsigned long long*)(p + 1024);
-    s.chunk_cnt = (unsigned int*)(p + 1024 + 256);
+    s.state = (unsigned long long*)(p + SEL_PASSES * SEL_BINS * 4);
+    s.chunk_cnt = (unsigned int*)(p + SEL_PASSES * SEL_BINS * 4 + 256);
     s.nchunk = (int)ceil_div(d, CHUNK);
     return s;
 }
 
 namespace {
-// The keep-th largest key into sc.state (8 radix passes); 0 < keep < d.
-hipError_t select_kth(const double* scores, int64_t d, int64_t keep, SelectScratch sc, hipStream_t st) {
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, st, sc.state, sc.hist, keep);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+// The keep-th largest key into sc.state; 0 < keep < d. Clears count if given.
+hipError_t select_kth(const double* scores, int64_t d, int64_t keep, SelectScratch sc, unsigned int* count,
+                      hipStream_t st) {
+    hipLaunchKernelGGL(k_select_init, dim3(SEL_PASSES * SEL_BINS / 256), dim3(256), 0, st, sc.state, sc.hist, keep,
+                       count);
+    // 16 keys per thread; every work-group flushes its histogram, so no more than
+    // fill the chip
     int64_t hgrid = ceil_div(d, 256 * 16);
-    if (hgrid > 2048) hgrid = 2048;
-    for (int pass = 0; pass < 8; ++pass) {
-        const int shift = 56 - 8 * pass;
-        hipLaunchKernelGGL(k_select_hist, dim3((unsigned)hgrid), dim3(256), 0, st, scores, d, sc.state, shift,
-                           sc.hist);
-        hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(256), 0, st, sc.state, sc.hist, shift);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    if (hgrid > 1024) hgrid = 1024;
+    for (int pass = 0; pass < SEL_PASSES; ++pass)
+        hipLaunchKernelGGL(k_select_hist, dim3((unsigned)hgrid), dim3(256), 0, st, scores, d, sc.state, pass, sc.hist);
+    hipLaunchKernelGGL(k_select_last, dim3(1), dim3(256), 0, st, sc.state, sc.hist);
+    return hipGetLastError();
 }
 }  // namespace
 
@@ -1075,9 +1145,8 @@ hipError_t launch_band_refine(const double* scores_in, int64_t d, int64_t keep, 
                               const float* L32, int mp, int64_t lstride, double lam, const float* theta,
                               double* diag, double* scores, int* err, hipStream_t st) {
     if (d <= 0 || keep <= 0 || keep >= d) return hipSuccess;  // the mask needs no cut
-    hipError_t e = select_kth(scores_in, d, keep, sc, st);
+    hipError_t e = select_kth(scores_in, d, keep, sc, count, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, count, 1, 0u);
     hipLaunchKernelGGL(k_band_collect, dim3((unsigned)ceil_div(d, 256)), dim3(256), 0, st, scores_in, d, sc.state,
                        tau, count, list);
     e = hipGetLastError();
@@ -1092,20 +1161,27 @@ hipError_t launch_band_refine(const double* scores_in, int64_t d, int64_t keep, 
     w.xmax = w.wmax + BR_ITERS * BR_SLOTS;
     const double mu = (double)m * lam;
     const unsigned rows16 = (unsigned)ceil_div(m, 16);
+    // Small blocks (G_b and L^-1 in at most 128 KB): one work-group refines a
+    // coordinate in about 20 us, the wide form's 25 launches take 80 us whatever
+    // the size.
+    const bool wide = (int64_t)m * (m > B ? m : B) > 32768;
+    if (!wide) w.x = nullptr;
     const int64_t ninit = (int64_t)BR_SLOTS * w.mq > BR_ITERS * BR_SLOTS ? (int64_t)BR_SLOTS * w.mq : BR_ITERS * BR_SLOTS;
-    hipLaunchKernelGGL(k_br_init, dim3((unsigned)ceil_div(ninit, 256)), dim3(256), 0, st, w);
-    for (int it = 0; it < BR_ITERS; ++it) {
-        if (it > 0)
-            hipLaunchKernelGGL(k_br_u, dim3((unsigned)ceil_div(B, 256), BR_SLOTS), dim3(1024), 0, st, G, m, d, B,
-                               count, list, w, it);
-        hipLaunchKernelGGL(k_br_r, dim3(rows16, BR_SLOTS), dim3(256), 0, st, G, m, d, B, count, list, w, mu, it);
-        hipLaunchKernelGGL(k_br_z, dim3(rows16, BR_SLOTS), dim3(256), 0, st, m, B, L32, mp, lstride, count, list, w,
-                           it);
-        hipLaunchKernelGGL(k_br_x, dim3((unsigned)ceil_div(m, 64), BR_SLOTS), dim3(256), 0, st, m, B, L32, mp,
-                           lstride, count, list, w, it);
+    if (wide) {
+        hipLaunchKernelGGL(k_br_init, dim3((unsigned)ceil_div(ninit, 256)), dim3(256), 0, st, w);
+        for (int it = 0; it < BR_ITERS; ++it) {
+            if (it > 0)
+                hipLaunchKernelGGL(k_br_u, dim3((unsigned)ceil_div(B, 256), BR_SLOTS), dim3(1024), 0, st, G, m, d, B,
+                                   count, list, w, it);
+            hipLaunchKernelGGL(k_br_r, dim3(rows16, BR_SLOTS), dim3(256), 0, st, G, m, d, B, count, list, w, mu, it);
+            hipLaunchKernelGGL(k_br_z, dim3(rows16, BR_SLOTS), dim3(256), 0, st, m, B, L32, mp, lstride, count, list, w,
+                               it);
+            hipLaunchKernelGGL(k_br_x, dim3((unsigned)ceil_div(m, 64), BR_SLOTS), dim3(256), 0, st, m, B, L32, mp,
+                               lstride, count, list, w, it);
+        }
+        hipLaunchKernelGGL(k_br_final, dim3(BR_SLOTS), dim3(256), 0, st, G, m, d, B, count, list, w, lam, tau, theta,
+                           diag, scores, err);
     }
-    hipLaunchKernelGGL(k_br_final, dim3(BR_SLOTS), dim3(256), 0, st, G, m, d, B, count, list, w, lam, tau, theta,
-                       diag, scores, err);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t lds = (size_t)(3 * ((m + 3) & ~3) + BAND_COLS) * sizeof(double);
@@ -1127,10 +1203,10 @@ hipError_t launch_topk_mask(const double* scores, int64_t d, int64_t keep, Selec
                            (uint8_t)(keep <= 0 ? 0 : 1));
         return hipGetLastError();
     }
-    hipError_t e = select_kth(scores, d, keep, sc, st);
+    hipError_t e = select_kth(scores, d, keep, sc, nullptr, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_tie_count, dim3(sc.nchunk), dim3(256), 0, st, scores, d, sc.state, sc.chunk_cnt);
-    hipLaunchKernelGGL(k_tie_scan, dim3(1), dim3(256), 0, st, sc.chunk_cnt, sc.nchunk);
+    hipLaunchKernelGGL(k_tie_scan, dim3(1), dim3(256), 0, st, sc.chunk_cnt, sc.nchunk, sc.state);
     hipLaunchKernelGGL(k_mask, dim3(sc.nchunk), dim3(256), 0, st, scores, d, sc.state, sc.chunk_cnt, mask);
     return hipGetLastError();
 }

@@ -146,3 +146,26 @@ def test_single_vector_units(dev, d, m):
     for t in range(3):
         assert rel_l2(Yn[t], orc.slide(Gn[t].numpy())) < F32_TOL
     assert win.status() == 0
+
+
+# keys over every digit of the selection: one value for all, two values, 36
+# decades, neighbouring doubles; fewer keys than a wave up to several rounds of
+# the grid; ranks at both ends and inside ties
+@pytest.mark.parametrize("fast", [False, True])
+@pytest.mark.parametrize("d,kind", [(4, "wide"), (1020, "ties"), (4100, "zeros"), (70_000, "wide"),
+                                    (70_000, "equal"), (300_004, "near"), (4_300_000, "ties")])
+def test_keep_mask_selection(dev, d, kind, fast):
+    """The mask against the oracle's ranking of the scores the call returns: exact."""
+    from oracle import mask as omask
+    from paper_2107_03356_amd import StaticBlocks
+    say("keep-mask selection", d, kind, fast)
+    g = torch.Generator().manual_seed(d)
+    u = torch.rand(d, generator=g)
+    theta = {"wide": 10.0 ** (36 * u - 18), "equal": torch.full((d,), 0.05), "zeros": torch.where(u < 0.6, 0.0, u),
+             "ties": torch.floor(u * 7), "near": 1.0 + u * 1e-3}[kind].float()
+    # one equal gradient row: every diagonal entry is the same
+    sb = StaticBlocks(torch.full((1, d), 0.01, device=dev), 4, 1e-2, fp32=fast)
+    for keep in sorted({1, d // 3, d // 2, d - 1} - {0}):
+        mask, scores = sb.obs_mask(theta.to(dev), keep)
+        assert sb.status() == 0
+        np.testing.assert_array_equal(mask.cpu().numpy(), omask.keep_mask(scores.cpu().numpy(), keep))
