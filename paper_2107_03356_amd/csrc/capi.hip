@@ -273,10 +273,13 @@ mfac_status window_factor(mfac_window w, const double* p, int pstride, int k) {
     return MFAC_OK;
 }
 
+// Whether the policy asks for a full refactor on the next replace.
+bool refactor_due(mfac_window w) { return w->period == 0 || w->since_refactor + 1 >= w->period; }
+
 // Coefficients after slot k took a gradient with Gram column p: O(m^2) update
 // of the inverse, or a full refactor when the policy asks for one.
 mfac_status window_slot_update(mfac_window w, int pstride, int k) {
-    if (w->period == 0 || w->since_refactor + 1 >= w->period) return window_factor(w, w->p, pstride, k);
+    if (refactor_due(w)) return window_factor(w, w->p, pstride, k);
     HIPCHK(launch_inv_replace(w->K, w->m, w->p, pstride, k, (double)w->m * w->lambda, w->Ainv, w->mp, w->zv,
                               w->zv + w->mp, w->err, w->st));
     w->since_refactor += 1;
@@ -288,7 +291,7 @@ mfac_status window_slot_update(mfac_window w, int pstride, int k) {
 // the same pass over Ainv.
 mfac_status window_slot_update_coef(mfac_window w, int pstride, int k, const double* rhs, int rstride, int nv, int kc,
                                     double s0, double s1) {
-    if (w->period == 0 || w->since_refactor + 1 >= w->period) {
+    if (refactor_due(w)) {
         mfac_status rc = window_factor(w, w->p, pstride, k);
         if (rc != MFAC_OK) return rc;
         HIPCHK(launch_coef_from_inv(w->Ainv, w->mp, w->m, rhs, rstride, nv, kc, s0, s1, w->coef, w->err, w->st));
@@ -433,6 +436,16 @@ MFAC_API mfac_status mfac_window_replace(mfac_window w, int32_t slot, const floa
     bool al = aligned16(g_new) && (y_out == nullptr || aligned16(y_out));
     for (int q = 0; q < n; ++q) vin.v[1 + q] = X + (int64_t)q * d;
     if (n > 0) al = al && aligned16(X) && aligned16(Y) && (d % 4 == 0);
+
+    // small window, no refactor due, no phases to trace: one launch
+    if (n == 0 && y_out && !w->trace && !refactor_due(w) && step_small(w->m, w->nslab) && launch_step_small) {
+        HIPCHK(launch_step_small(w->G, w->m, d, w->nslab, k, g_new, y_out, al, (double)w->m * w->lambda, w->K, w->Ainv,
+                                 w->mp, w->err, w->st));
+        w->since_refactor += 1;
+        if (slot < 0) w->head = (k + 1) % w->m;
+        w->steps += 1;
+        return MFAC_OK;
+    }
 
     Pass1Grid grid{};
     HIPCHK(mark_begin(w));

@@ -550,6 +550,110 @@ __global__ __launch_bounds__(256) void k_write_row(float* __restrict__ G, int m,
     *reinterpret_cast<float4*>(G + slab * (int64_t)m * SLAB + (int64_t)k * SLAB + (j - slab * SLAB)) = v;
 }
 
+// A whole sliding step of a small window (m <= 64) in one work-group: the new
+// row and its Gram column, the slot update of Ainv, its new column k as the
+// coefficients, and y. Separate kernels run 2 to 5 us each on such a window,
+// nearly all of it launch and latency (a step at d = 4096, m = 16: six launches
+// 22 us, this 12 us). The order of the m x m arithmetic is that of k_inv_gemv and
+// k_inv_update_coef except for the order of the sums; every sum is fp64.
+constexpr int SMALL_M = 64, SMALL_T = 1024, SMALL_W = SMALL_T / 64;
+
+__global__ __launch_bounds__(SMALL_T) void k_step_small(float* __restrict__ G, int m, int64_t d, int ncolpad, int k,
+                                                        const float* __restrict__ g, float* __restrict__ y, int aligned,
+                                                        double mu, double* __restrict__ K, double* __restrict__ Ainv,
+                                                        int mp, int* __restrict__ err) {
+    __shared__ double Ai[SMALL_M][SMALL_M + 1];
+    __shared__ double part[SMALL_M + SMALL_W], p[SMALL_M], z[SMALL_M], w[SMALL_M], v[SMALL_M], cf[SMALL_M];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int e = tid; e < SMALL_M * SMALL_M; e += SMALL_T)
+        if ((e >> 6) < m) Ai[e >> 6][e & 63] = Ainv[(int64_t)(e >> 6) * mp + (e & 63)];
+    // Gram column: tasks of one row and one of nseg column ranges per wave
+    const int nseg = m >= SMALL_W ? 1 : SMALL_W / m;
+    const int nq = ncolpad / 256;  // wave-wide quads per row
+    for (int t = wave; t < m * nseg; t += SMALL_W) {
+        const int i = t / nseg, sg = t - i * nseg;
+        double s = 0.0;
+#pragma unroll 4
+        for (int q = nq * sg / nseg; q < nq * (sg + 1) / nseg; ++q) {
+            const int j = q * 256 + lane * 4;
+            float4 r = ld4(g, j, d, aligned);
+            const float4 gq = r;
+            float* gp = G + (int64_t)(j / SLAB) * m * SLAB + (int64_t)i * SLAB + j % SLAB;
+            if (i == k)
+                *reinterpret_cast<float4*>(gp) = gq;
+            else
+                r = *reinterpret_cast<const float4*>(gp);
+            s = dot4d(r, gq, s);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) part[t] = s;
+    }
+    __syncthreads();
+    if (tid < m) {
+        double s = 0.0;
+        for (int sg = 0; sg < nseg; ++sg) s += part[tid * nseg + sg];
+        p[tid] = s;
+        v[tid] = Ai[k][tid];
+        K[(int64_t)k * m + tid] = s;
+        K[(int64_t)tid * m + k] = s;
+        if (!isfinite(s)) atomicOr(err, 1);
+    }
+    __syncthreads();
+    // z = Ainv b (b = p off slot k, 0 at k): 16 threads per row
+    {
+        const int i = tid >> 4, c = tid & 15;
+        double s = 0.0;
+        if (i < m)
+            for (int j = c; j < m; j += 16)
+                if (j != k) s += Ai[i][j] * p[j];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (i < m && c == 0) z[i] = s;
+    }
+    __syncthreads();
+    const double t = v[k], r = z[k] / t;
+    // s = p_k + mu - b^T (z - v r), every wave for itself
+    double bu = lane < m && lane != k ? p[lane] * (z[lane] - v[lane] * r) : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) bu += __shfl_xor(bu, o, 64);
+    const double s = p[k] + mu - bu;
+    if (tid == 0 && (!(s > 0.0) || !isfinite(s) || !(t > 0.0))) atomicOr(err, 16);
+    if (tid < m) w[tid] = z[tid] - v[tid] * r - (tid == k ? 1.0 : 0.0);
+    __syncthreads();
+    const double it = 1.0 / t, is = 1.0 / s;
+    for (int e = tid; e < SMALL_M * SMALL_M; e += SMALL_T) {
+        const int i = e >> 6, j = e & 63;
+        if (i < m && j < m) {
+            const double a = Ai[i][j] - v[i] * v[j] * it + w[i] * w[j] * is;
+            Ainv[(int64_t)i * mp + j] = a;
+            if (j == k) {
+                const double c = a * -(double)m;
+                if (!isfinite(c)) atomicOr(err, 4);
+                cf[i] = c;
+            }
+        }
+    }
+    __syncthreads();
+    // y = -G^T cf; row k is g
+    for (int j = tid * 4; j < d; j += SMALL_T * 4) {
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+        const float* gp = G + (int64_t)(j / SLAB) * m * SLAB + j % SLAB;
+        const float4 gq = ld4(g, j, d, aligned);
+#pragma unroll 8
+        for (int i = 0; i < m; ++i) {
+            float4 q = *reinterpret_cast<const float4*>(gp + (int64_t)(i == k ? (k > 0 ? 0 : m - 1) : i) * SLAB);
+            if (i == k) q = gq;
+            const double c = cf[i];
+            a0 = fma(c, (double)q.x, a0);
+            a1 = fma(c, (double)q.y, a1);
+            a2 = fma(c, (double)q.z, a2);
+            a3 = fma(c, (double)q.w, a3);
+        }
+        st4(y, j, d, aligned, make_float4((float)(0.0 - a0), (float)(0.0 - a1), (float)(0.0 - a2), (float)(0.0 - a3)));
+    }
+}
+
 template <int NV>
 struct PassCfg {
     // Pass 1: U float4 per lane and row (the vector chunks stay in registers),
@@ -728,6 +832,14 @@ hipError_t launch_get_rows(const float* G, int m, int64_t d, int first, int coun
     const bool aligned = ((uintptr_t)rows % 16 == 0) && (ld % 4 == 0);
     dim3 grid((unsigned)ceil_div(ceil_div(d, 4), 256), (unsigned)count);
     hipLaunchKernelGGL(k_get_rows, grid, dim3(256), 0, st, G, m, d, first, rows, ld, aligned ? 1 : 0);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_small(float* G, int m, int64_t d, int64_t nslab, int k, const float* g, float* y, bool aligned,
+                             double mu, double* K, double* Ainv, int mp, int* err, hipStream_t st) {
+    if (!step_small(m, nslab)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_step_small, dim3(1), dim3(SMALL_T), 0, st, G, m, d, (int)(nslab * SLAB), k, g, y,
+                       aligned ? 1 : 0, mu, K, Ainv, mp, err);
     return hipGetLastError();
 }
 

@@ -169,3 +169,37 @@ def test_keep_mask_selection(dev, d, kind, fast):
         mask, scores = sb.obs_mask(theta.to(dev), keep)
         assert sb.status() == 0
         np.testing.assert_array_equal(mask.cpu().numpy(), omask.keep_mask(scores.cpu().numpy(), keep))
+
+
+# the one-launch step of small windows: rows in 8 column ranges, rows that 16
+# waves do not divide, the largest windows it takes and the first it does not, vectors off 16-byte alignment
+@pytest.mark.parametrize("d,m,off", [(32_768, 2, 0), (40_000, 1, 0), (5, 32, 1), (5, 64, 1), (2049, 15, 0), (2048, 32, 3), (4095, 16, 1),
+                                     (4096, 17, 0)])
+def test_small_window_step(dev, d, m, off):
+    from paper_2107_03356_amd import Window
+    say("small window d =", d, "m =", m, "offset", off)
+    gs = _stream(d, m, 1e-3, seed=d + m)
+    win, orc = Window(d, m, 1e-3, max_queries=1, device=dev), WindowOracle(d, m, 1e-3)
+    win.set_refactor_period(7)
+    gbuf, ybuf = torch.empty(d + 4, device=dev), torch.full((d + 4,), 7.0, device=dev)
+    for t in range(2 * m + 9):
+        g = gs.row(t)
+        gbuf[off:off + d] = g.to(dev)
+        if t % 5 == 4:   # the separate kernels between two one-launch steps
+            x = gs.queries(t, 1)
+            y, Y = win.replace(gbuf[off:off + d].clone(), X=x.to(dev))
+            yo = orc.slide(g.numpy())
+            assert rel_l2(Y.cpu().numpy()[0], orc.ihvp(x.numpy())[0]) < F32_TOL
+        elif t % 5 == 3:   # the slot given
+            head, steps = win.info()
+            y = win.replace(gbuf[off:off + d], slot=head, y_out=ybuf[off:off + d])
+            assert win.info() == (head, steps + 1)
+            win.set_head((head + 1) % m, steps + 1)
+            yo = orc.slide(g.numpy())
+        else:
+            y = win.replace(gbuf[off:off + d], y_out=ybuf[off:off + d])
+            yo = orc.slide(g.numpy())
+        assert rel_l2(y.cpu().numpy(), yo) < F32_TOL, t
+        assert win.status() == 0
+        assert float(ybuf[off + d]) == 7.0 and (off == 0 or float(ybuf[off - 1]) == 7.0)
+    np.testing.assert_array_equal(win.get_rows(0, 1).cpu().numpy()[0], orc.G[0].astype(np.float32))
