@@ -100,8 +100,11 @@ constexpr int NSP = 20;   // LDS pitch of the 16-column product scratch
 //   Cholesky, 16-column panels left to right: wave 0 factors the panel's
 //     diagonal block and inverts it in the same column sweep (a lane per row
 //     of L and per column of the inverse D); the rows below are A D^T, and
-//     the four waves apply the panel's rank-16 update to the lower tiles to
-//     its right, both on MFMA;
+//     the panel's rank-16 update goes to the lower tiles to its right, both
+//     on MFMA. The diagonal blocks are the chain that bounds one node (51 of
+//     132 thousand cycles at n = 128 in fp64): wave 0 updates and factors
+//     the next one while the other waves apply the rest of the update
+//     (one matrix: 55 -> 49 us a node);
 //   inverse of the factor in place, block columns right to left:
 //     Linv[below j][j] = -Linv[below j][below j] L[below j][j] D_j,
 //     where the first factor is already the inverse (two MFMA products).
@@ -152,52 +155,53 @@ __global__ __launch_bounds__(256) void k_factor_node(const R* __restrict__ A, R*
     __syncthreads();
 
     int bad = 0;
-    for (int p = 0; p < np; ++p) {
-        const int j0 = p * 16;
-        if (wave == 0) {
-            // the 16 x 16 diagonal block: lane l < 16 keeps row l of it (r) and
-            // column l of its inverse (x, by forward substitution folded into
-            // the same column sweep); column k of L goes to every lane through
-            // LDS. Lanes 16..63 and entries above the diagonal carry values
-            // that nothing reads.
-            R r[16], x[16];
+    auto factor_diag = [&](int j0) {
+        // the 16 x 16 diagonal block: lane l < 16 keeps row l of it (r) and
+        // column l of its inverse (x, by forward substitution folded into
+        // the same column sweep); column k of L goes to every lane through
+        // LDS. Lanes 16..63 and entries above the diagonal carry values
+        // that nothing reads.
+        R r[16], x[16];
 #pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                r[c] = lane < 16 ? X[j0 + lane][j0 + c] : R(0);
-                x[c] = (c == lane) ? R(1) : R(0);
-            }
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                R pk = lane_value(r[k], k);
-                if (!(pk > R(0)) || !isfinite(pk)) {
-                    bad = 1;
-                    pk = R(1);
-                }
-                const R rs = rsqrt_of(pk);
-                r[k] = lane == k ? pk * rs : r[k] * rs;
-                if (lane < 16) colv[k & 1][lane] = r[k];
-                wave_sync();
-                R lc[16];
-#pragma unroll
-                for (int c = 0; c < 16; ++c) lc[c] = colv[k & 1][c];
-                // x_k = (e_l - sum_{i<k} L[k][i] x_i)_k / L[k][k], then the
-                // rows below take their L[.][k] x_k terms
-                x[k] = x[k] * rs;
-#pragma unroll
-                for (int c = k + 1; c < 16; ++c) {
-                    r[c] -= r[k] * lc[c];
-                    x[c] -= lc[c] * x[k];
-                }
-                wave_sync();
-            }
-            // the inverse block (zeros above its diagonal) over the block
-            if (lane < 16) {
-#pragma unroll
-                for (int c = 0; c < 16; ++c) X[j0 + c][j0 + lane] = x[c];
-            }
+        for (int c = 0; c < 16; ++c) {
+            r[c] = lane < 16 ? X[j0 + lane][j0 + c] : R(0);
+            x[c] = (c == lane) ? R(1) : R(0);
         }
-        __syncthreads();
-        const int nt = np - 1 - p;  // 16-row tiles below the diagonal block
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            R pk = lane_value(r[k], k);
+            if (!(pk > R(0)) || !isfinite(pk)) {
+                bad = 1;
+                pk = R(1);
+            }
+            const R rs = rsqrt_of(pk);
+            r[k] = lane == k ? pk * rs : r[k] * rs;
+            if (lane < 16) colv[k & 1][lane] = r[k];
+            wave_sync();
+            R lc[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c) lc[c] = colv[k & 1][c];
+            // x_k = (e_l - sum_{i<k} L[k][i] x_i)_k / L[k][k], then the
+            // rows below take their L[.][k] x_k terms
+            x[k] = x[k] * rs;
+#pragma unroll
+            for (int c = k + 1; c < 16; ++c) {
+                r[c] -= r[k] * lc[c];
+                x[c] -= lc[c] * x[k];
+            }
+            wave_sync();
+        }
+        // the inverse block (zeros above its diagonal) over the block
+        if (lane < 16) {
+#pragma unroll
+            for (int c = 0; c < 16; ++c) X[j0 + c][j0 + lane] = x[c];
+        }
+    };
+    // step p: the panel of column block p and its update (none at p = -1), then
+    // diagonal block p + 1
+    for (int p = -1; p < np - 1; ++p) {
+        const int j0 = p * 16;
+        const int nt = p < 0 ? 0 : np - 1 - p;  // 16-row tiles below the diagonal block
         // panel rows below: L = A D^T (D the diagonal block's inverse), into S
         for (int t = wave; t < nt; t += 4) {
             acc_t acc = acc_t{0, 0, 0, 0};
@@ -209,10 +213,11 @@ __global__ __launch_bounds__(256) void k_factor_node(const R* __restrict__ A, R*
             for (int rr = 0; rr < 4; ++rr) S[16 * t + M::row(lane, rr)][rl] = acc[rr];
         }
         __syncthreads();
-        // lower 16 x 16 tiles (a, b), a >= b, of the trailing block -= P P^T,
-        // and the panel rows back into X
+        // lower 16 x 16 tiles (a, b), a >= b, of the trailing block -= P P^T. Wave 0
+        // takes the first, which is the next diagonal block, and factors it while
+        // the other waves update the rest and put the panel rows back into X.
         const int ntl = nt * (nt + 1) / 2;
-        for (int q = wave; q < ntl; q += 4) {
+        for (int q = wave; q < (wave == 0 ? min(1, ntl) : ntl); q += 3) {
             int a = 0;
             while ((a + 1) * (a + 2) / 2 <= q) ++a;
             const int b = q - a * (a + 1) / 2;
@@ -226,14 +231,22 @@ __global__ __launch_bounds__(256) void k_factor_node(const R* __restrict__ A, R*
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) X[ra + M::row(lane, rr)][cb + rl] = acc[rr];
         }
-        for (int e = tid; e < nt * 256; e += 256) X[j0 + 16 + (e >> 4)][j0 + (e & 15)] = S[e >> 4][e & 15];
+        if (wave == 0) {
+            wave_sync();
+            factor_diag(j0 + 16);
+        } else {
+            for (int e = tid - 64; e < nt * 256; e += 192) X[j0 + 16 + (e >> 4)][j0 + (e & 15)] = S[e >> 4][e & 15];
+        }
         __syncthreads();
     }
 
     // block columns right to left
     for (int j = np - 2; j >= 0; --j) {
         const int nt = np - 1 - j, rb = 16 * (j + 1);
-        for (int t = wave; t < nt; t += 4) {
+        // a wave takes a long sum and a short one (nt <= 7)
+        for (int h = 0; h < 2; ++h) {
+            const int t = h == 0 ? nt - 1 - wave : nt - 8 + wave;
+            if (t < 0) continue;
             acc_t acc = acc_t{0, 0, 0, 0};
             for (int s = 0; s <= t; ++s)
 #pragma unroll
