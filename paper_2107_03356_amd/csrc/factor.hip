@@ -15,7 +15,10 @@
 // Every GEMM is batched over the matrices and skips the K-range its
 // triangular operand makes zero, so the flops are m^3/3 for the factor and
 // m^3/3 for the inverse, nearly all of it in large MFMA tiles.
+#include <type_traits>
+
 #include "internal.h"
+#include "split_mfma.h"
 #include "tile_util.h"
 
 namespace mfac {
@@ -358,6 +361,128 @@ __global__ __launch_bounds__(256) void k_bgemm_reduce(GemmArgs<T> g) {
         if (col + k < g.N) dst[k] = g.beta != 0.0 ? (T)g.alpha * v[k] + (T)g.beta * dst[k] : (T)g.alpha * v[k];
 }
 
+// The products with a lower triangular A (KHI_ROW, A stored by row) of the fast
+// static mode's large levels: 256 x 256 tiles, fp32 products on the bf16 matrix
+// cores (split_mfma.h), eight waves of 128 x 64 with the schedule of
+// k_gram_blocks32. 32 x 32 pieces outside M x N are skipped, and in the diagonal
+// tile a piece stops at its own rows (waves w and w + 4 share a SIMD: upper and
+// lower rows are paired there). Against the fp32 MFMA on 128-tiles, a batch of
+// 512: 512^3 products 720 and 747 -> 650 us, 256^3 127 -> 103 us. Grid:
+// tiles * nbatch, the longest rows first.
+template <bool TB>
+__global__ __launch_bounds__(512, 2) void k_bgemm_split(GemmArgs<float> g) {
+    constexpr int BT = 256, WM = 128, WN = 64, NX = WM / 32, NY = WN / 32, KC = SPLIT_KC;
+    __shared__ SplitChunk<BT> As[2], Bs[2];
+    const int lid = xcd_remap(blockIdx.x, gridDim.x);
+    const int bt = lid / g.ntask, t = lid - bt * g.ntask;
+    const int I = g.tiles_m - 1 - t / g.tiles_n, J = t % g.tiles_n;
+    const float* __restrict__ A = g.A + (int64_t)bt * g.bstride + (int64_t)g.a0r * g.ld + g.a0c;
+    const float* __restrict__ B = g.B + (int64_t)bt * g.bstride + (int64_t)g.b0r * g.ld + g.b0c;
+    float* __restrict__ C = g.C + (int64_t)bt * g.bstride;
+    const int ld = g.ld, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 2, wc = wave & 3;
+    const int m0 = I * BT, n0 = J * BT;
+    const int khi = min(g.K, m0 + BT);
+
+    // staging of a 16-deep chunk. Operands stored by row: k 4 (tid % 4) .. +3 of
+    // rows tid / 4 and 128 + tid / 4; B stored by k: k 8 (tid / 256) .. +7 of
+    // column tid % 256. Clamped, in-bounds addresses: what lies outside is
+    // skipped or dropped.
+    const int sr = tid >> 2, sq = tid & 3, sc = tid & 255, sh = wave >> 2;
+    const float* a0 = A + (int64_t)min(m0 + sr, g.M - 1) * ld + sq * 4;
+    const float* a1 = A + (int64_t)min(m0 + 128 + sr, g.M - 1) * ld + sq * 4;
+    const float* b0 = B + (int64_t)min(n0 + sr, g.N - 1) * ld + sq * 4;
+    const float* b1 = B + (int64_t)min(n0 + 128 + sr, g.N - 1) * ld + sq * 4;
+    const unsigned bc = (unsigned)min(n0 + sc, g.N - 1);
+    float4 qa[2], qb[2];
+    auto load = [&](int k0) {
+        const int k = min(k0, g.K - KC);
+        qa[0] = *reinterpret_cast<const float4*>(a0 + k);
+        qa[1] = *reinterpret_cast<const float4*>(a1 + k);
+        if constexpr (TB) {
+            qb[0] = *reinterpret_cast<const float4*>(b0 + k);
+            qb[1] = *reinterpret_cast<const float4*>(b1 + k);
+        } else {
+            const float* r = B + (int64_t)(k + sh * 8) * ld;
+#pragma unroll
+            for (int h = 0; h < 2; ++h, r += 4 * (int64_t)ld)
+                qb[h] = make_float4(r[bc], (r + ld)[bc], (r + 2 * (int64_t)ld)[bc], (r + 3 * (int64_t)ld)[bc]);
+        }
+    };
+    auto store = [&](int buf) {
+        As[buf].put4(sr, sq, qa[0]);
+        As[buf].put4(128 + sr, sq, qa[1]);
+        if constexpr (TB) {
+            Bs[buf].put4(sr, sq, qb[0]);
+            Bs[buf].put4(128 + sr, sq, qb[1]);
+        } else {
+            Bs[buf].put8(sc, sh, f8v{qb[0].x, qb[0].y, qb[0].z, qb[0].w, qb[1].x, qb[1].y, qb[1].z, qb[1].w});
+        }
+    };
+
+    v16f acc[NX][NY];
+    unsigned in = 0;  // pieces inside M x N
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int y = 0; y < NY; ++y) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[x][y][q] = 0.f;
+            if (m0 + wr * WM + 32 * x < g.M && n0 + wc * WN + 32 * y < g.N) in |= 1u << (x * NY + y);
+        }
+    auto below = [&](int k) {
+        unsigned mk = 0;
+#pragma unroll
+        for (int x = 0; x < NX; ++x)
+            if (k < m0 + wr * WM + 32 * x + 32) mk |= ((1u << NY) - 1) << (x * NY);
+        return in & mk;
+    };
+    load(0);
+    store(0);
+    load(KC);
+    __syncthreads();
+    const bool early = wave < 4;
+    int k0 = 0;
+    auto walk = [&](auto all, int kend) {
+        auto step = [&](int buf, int k) {
+            if (early) {
+                store(buf ^ 1);
+                load(k + 2 * KC);
+            }
+            split_mma<decltype(all)::value>(As[buf], Bs[buf], wr * WM, wc * WN, lane,
+                                            decltype(all)::value ? 0u : below(k), acc);
+            if (!early) {
+                store(buf ^ 1);
+                load(k + 2 * KC);
+            }
+            __syncthreads();
+        };
+        for (; k0 < kend; k0 += 2 * KC) {
+            step(0, k0);
+            step(1, k0 + KC);
+        }
+    };
+    // left of the diagonal tile, unless the tile is ragged (the same choice for
+    // the whole work-group); then the rest
+    if (m0 + BT <= g.M && n0 + BT <= g.N) walk(std::true_type{}, min(khi, m0));
+    walk(std::false_type{}, khi);
+
+    const float al = (float)g.alpha;
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int y = 0; y < NY; ++y) {
+            if (!((in >> (x * NY + y)) & 1u)) continue;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const int row = m0 + wr * WM + 32 * x + mfma32x32_row(lane, q);
+                const int col = n0 + wc * WN + 32 * y + (lane & 31);
+                C[(int64_t)(g.cm0 + row) * ld + g.cn0 + col] = al * acc[x][y][q];
+            }
+        }
+}
+
 template <typename T, int BT>
 void launch_bgemm(bool ta, bool tb, int64_t grid, const GemmArgs<T>& g, hipStream_t st) {
     if (!ta && !tb) hipLaunchKernelGGL((k_bgemm<T, false, false, BT>), dim3((unsigned)grid), dim3(4 * BT), 0, st, g);
@@ -388,6 +513,28 @@ hipError_t gemm(bool ta, bool tb, const T* A, int a0r, int a0c, const T* B, int 
     g.alpha = alpha;
     g.beta = beta;
     g.flags = flags;
+    // fp32, a large level of a batch, A stored by row: bf16 parts in 256 x 256
+    // tiles, as long as they are enough work-groups for half the chip. (With A
+    // and B both stored by k the 16 four-byte loads per chunk and thread take
+    // more than the MFMAs give: 830 -> 900 us.)
+    if constexpr (sizeof(T) == 4) {
+        const int64_t tm = ceil_div(M, 256), tn = ceil_div(N, 256);
+        if (!ta && flags == KHI_ROW && beta == 0.0 && M >= 256 && N >= 256 && tm * tn * nbatch >= 128) {
+            g.tiles_m = (int)tm;
+            g.tiles_n = (int)tn;
+            g.mode = TASK_PLAIN;
+            g.ntask = (int)(tm * tn);
+            g.nsplit = 1;
+            g.nbatch = nbatch;
+            g.part = nullptr;
+            const dim3 grid((unsigned)((int64_t)g.ntask * nbatch));
+            if (tb)
+                hipLaunchKernelGGL(k_bgemm_split<true>, grid, dim3(512), 0, st, g);
+            else
+                hipLaunchKernelGGL(k_bgemm_split<false>, grid, dim3(512), 0, st, g);
+            return hipGetLastError();
+        }
+    }
     // 64 x 64 tiles (four waves, four work-groups per CU) for products of at
     // most 256 x 256, the recursion's short levels, where 128 x 128 tiles
     // leave one or four tiles per matrix: 7-8% off the 256 x 256 level in
