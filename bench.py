@@ -86,7 +86,7 @@ def read_counters(workload, kernel):
 
 
 STATIC_SRC = [os.path.join(ROOT, "paper_2107_03356_amd", "csrc", f)
-              for f in ("gram.hip", "static.hip", "factor.hip", "chol.hip", "tile_util.h")]
+              for f in ("gram.hip", "static.hip", "factor.hip", "chol.hip", "tile_util.h", "split_mfma.h")]
 
 
 def read_static_counters(workload, kernel):
@@ -193,12 +193,14 @@ def bench_static(args, wl, dev):
     P.load()
     d, m, B = wl.d, wl.m, wl.block
     paged = wl.page_cols > 0
-    # the fast mode (fp32 matrix cores, exact mask) wherever it applies
+    # the fast mode (fp32, exact mask) wherever it applies
     fast = not args.fp64 and not paged and m <= 4096 and B <= 65536
     # algorithmic flops per run: symmetric Gram m^2 B and triangular W = L^-1 G_b
     # m^2 B per block (2 m^2 d together), Cholesky and triangular inverse m^3/3 each
     flops = 2.0 * m * m * d + 2.0 * (m ** 3 / 3.0) * (d // B)
-    mfma_peak = 157.3 if fast else 78.6   # the dominant kernel's dtype: fp32 or fp64 matrix cores
+    # the dominant kernel's rate: fp32 products of six bf16 MFMA products each
+    # (2500 TFLOP/s dense), or fp64 matrix cores
+    mfma_peak = 2500.0 / 6 if fast else 78.6
     t0 = time.perf_counter()
     gs = GradientStream(wl, seed=args.seed, device=dev)
     G0 = torch.empty((m, d), dtype=torch.float32, device=dev)
@@ -319,7 +321,7 @@ def bench_static(args, wl, dev):
         "dtype": "f32" if fast else "f64", "data": "synthetic",
         "config": {"workload": wl.name, "d": d, "m": m, "block": B, "lambda": wl.lam, "keep": keep,
                    "page_cols": wl.page_cols or None,
-                   "mode": ("fast: Gram, factor and W on fp32 matrix cores, fp64 band re-decided at the cut"
+                   "mode": ("fast: Gram, factor and W in fp32 (large products as bf16 parts), fp64 band re-decided at the cut"
                             if fast else "fp64 matrix cores throughout")},
         "roofline": {"bound": "mfma", "kernel": gram_kernel, "achieved": gram_tf, "peak": mfma_peak,
                      "unit": "TFLOP/s", "frac": gram_tf / mfma_peak,

@@ -248,8 +248,8 @@ mfac_status mfac_static_precompute(mfac_static* out, int64_t d, int32_t block, i
 #define MFAC_STATIC_TRACE 1u /* record HIP events around the precompute's stages and
                                 mfac_obs_mask; read with mfac_static_trace_read */
 /* Fast mode (mfac_static_precompute only; m <= 4096, block <= 65536): the
- * Gram matrices, their Cholesky factors and inverses, and W on fp32 matrix
- * cores (fp32 products and sums: a Gram entry over at most 2048 columns,
+ * Gram matrices, their Cholesky factors and inverses, and W in fp32 (products
+ * and sums; large products as exact bf16 parts on the matrix cores: a Gram entry over at most 2048 columns,
  * wider blocks adding their 2048-column splits in fp64; W over the m rows;
  * the squares of W summed in fp64 for the diagonal). The inverse diagonal then
  * carries the fp32 rounding (on gradient-like data with a well-conditioned

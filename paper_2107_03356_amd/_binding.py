@@ -276,7 +276,7 @@ class StaticBlocks:
     """Static block-wise precompute over a caller's m x d gradient matrix.
 
     G is overwritten in place by W (W_b = R_b^-1 G_b per block), except with
-    ``fp32=True`` (the fast mode: fp32 matrix cores, G left intact, W formed in
+    ``fp32=True`` (the fast mode: fp32, G left intact, W formed in
     the workspace by the first query, the keep-mask still exact). G is either a
     device tensor, or (``page_cols`` given) a pinned host tensor
     (``pin_memory=True``) larger than the device should hold: it then passes

@@ -109,7 +109,7 @@ struct mfac_static_s {
     int B, m, mp, nblocks, batch;
     double lambda;
     float* G;
-    // fast mode (MFAC_STATIC_FP32): fp32 MFMA Gram and W, the fp32 L^-1 of every
+    // fast mode (MFAC_STATIC_FP32): fp32 Gram and W, the fp32 L^-1 of every
     // block kept, G left intact, W formed on the first query into its own
     // buffer; the keep-mask's band recomputed exactly in fp64
     bool fast, w_ready;

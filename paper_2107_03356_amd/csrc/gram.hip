@@ -18,8 +18,8 @@
 // the full-d precompute of Section 3.1) the block's columns are also split
 // over work-groups and the fp64 partial tiles are summed in split order by
 // k_gram_blocks_reduce.
-// The fast static mode's k_gram_blocks32 runs the block Gram on fp32 MFMA in
-// 256 x 256 tiles (see there).
+// The fast static mode's k_gram_blocks32 runs the block Gram in fp32 on the bf16
+// matrix cores (see there).
 #include <type_traits>
 
 #include "internal.h"

@@ -94,7 +94,7 @@ int64_t gram_blocks_part_doubles(int nb, int mp, int B);
 hipError_t launch_gram_blocks(const float* G, int m, int64_t d, int B, int b0, int nb,
                               double mu, double* A, int mp, double* part, hipStream_t st,
                               bool accumulate = false);
-// The same on fp32 MFMA in 256 x 256 tiles (fp32 sums over at most 2048
+// The same in fp32, on bf16 parts (split_mfma.h; fp32 sums over at most 2048
 // columns, longer blocks split and the splits summed in fp64), stored as fp32
 // A; no accumulate mode. part: gram_blocks32_part_doubles(nb, mp, B).
 int64_t gram_blocks32_part_doubles(int nb, int mp, int B);
@@ -118,7 +118,7 @@ hipError_t launch_assemble(double* K, int m, const double* p, int pstride, int k
 hipError_t launch_factor_invert(double* A, double* Linv, int mp, int nbatch, int64_t bstride, int* err,
                                 hipStream_t st, double* part = nullptr, int64_t part_elems = 0);
 int64_t splitk_part_doubles(int mp);
-// The same in fp32 (fp32 matrix cores and leaves), for the fast static mode.
+// The same in fp32 (matrix cores and leaves), for the fast static mode.
 hipError_t launch_factor_invert32(float* A, float* Linv, int mp, int nbatch, int64_t bstride, int* err,
                                   hipStream_t st);
 // Ainv = Linv^T Linv (the explicit inverse of A = L L^T), full mp x mp.
@@ -143,7 +143,7 @@ hipError_t launch_coef_from_inv(const double* Ainv, int mp, int m, const double*
 hipError_t launch_trmm_diag(const double* Linv, int mp, int64_t bstride, float* G, int m,
                             int64_t d, int B, int b0, int nb, double lam, double* diag,
                             hipStream_t st);
-// W_b = Linv_b G_b on fp32 MFMA for blocks [b0, b0+nb): Linv the fp32 L^-1
+// W_b = Linv_b G_b in fp32 (bf16 parts) for blocks [b0, b0+nb): Linv the fp32 L^-1
 // of each block at batch stride lstride; G is read only. diag (or nullptr):
 // (1 - colsum(W^2)) / lam in fp64 from the fp32 W. Wout (or nullptr): W, row
 // stride d.
