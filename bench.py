@@ -249,9 +249,8 @@ def bench_static(args, wl, dev):
     mask_last = mask.cpu().numpy()
     diag_last = sb.inv_diag(fp64=True).cpu().numpy()
 
-    # queries on the finished precompute (W in place of G, or formed into the
-    # workspace by the first query in the fast mode): block-wise IHVP with 1
-    # and 4 vectors, and the OBS correction for the keep-mask's complement
+    # queries on the finished precompute (W in place of G, or in the workspace in
+    # the fast mode): block-wise IHVP with 1 and 4 vectors, and the OBS correction for the keep-mask's complement
     queries = {}
     X = torch.empty((4, d), dtype=torch.float32, device=dev)
     for q in range(4):

@@ -254,10 +254,9 @@ mfac_status mfac_static_precompute(mfac_static* out, int64_t d, int32_t block, i
  * the squares of W summed in fp64 for the diagonal). The inverse diagonal then
  * carries the fp32 rounding (on gradient-like data with a well-conditioned
  * G_b G_b^T + m*lambda*I, a largest entry error of 4.1e-6 relative measured
- * at d = 4.19M, B = 2048, m = 1024). G is left intact: the fp32 L^-1 of
- * every block is kept in the workspace, and W is formed into the workspace by
- * the first query that reads it (mfac_static_ihvp, mfac_static_element;
- * mfac_obs_update uses W if it is there, and otherwise G and L^-1). mfac_obs_mask stays exact: coordinates whose fp64 score
+ * at d = 4.19M, B = 2048, m = 1024). G is left intact: W and the fp32
+ * L^-1 of every block go into the workspace. Of the later calls only
+ * mfac_obs_mask reads G. mfac_obs_mask stays exact: coordinates whose fp64 score
  * lies within 1e-5 relative of the cut get their diagonal recomputed in fp64
  * (iterative refinement against G, see mfac_obs_mask), so the mask equals the
  * fp64 mask whenever the fp32 path's score error is below about 1e-5. */

@@ -276,8 +276,8 @@ class StaticBlocks:
     """Static block-wise precompute over a caller's m x d gradient matrix.
 
     G is overwritten in place by W (W_b = R_b^-1 G_b per block), except with
-    ``fp32=True`` (the fast mode: fp32, G left intact, W formed in
-    the workspace by the first query, the keep-mask still exact). G is either a
+    ``fp32=True`` (the fast mode: fp32, G left intact, W in
+    the workspace, the keep-mask still exact). G is either a
     device tensor, or (``page_cols`` given) a pinned host tensor
     (``pin_memory=True``) larger than the device should hold: it then passes
     through the device in pages of ``page_cols`` columns (whole blocks when

@@ -110,9 +110,9 @@ struct mfac_static_s {
     double lambda;
     float* G;
     // fast mode (MFAC_STATIC_FP32): fp32 Gram and W, the fp32 L^-1 of every
-    // block kept, G left intact, W formed on the first query into its own
-    // buffer; the keep-mask's band recomputed exactly in fp64
-    bool fast, w_ready;
+    // block kept, G left intact, W in a buffer of its own; the keep-mask's band
+    // recomputed exactly in fp64
+    bool fast;
     float* W;  // where the queries read W: G (fp64 mode) or the W buffer (fast mode)
     float* A32;  // fast mode: the batch of fp32 Gram matrices, factored in place
     float* L32;  // fast mode: fp32 L^-1 of every block (the factor writes it here)
@@ -868,7 +868,7 @@ MFAC_API mfac_status mfac_static_precompute(mfac_static* out, int64_t d, int32_t
     for (int b0 = 0; b0 < s->nblocks; b0 += s->batch) {
         const int nb = (s->nblocks - b0) < s->batch ? (s->nblocks - b0) : s->batch;
         // fast mode: fp32 Gram, fp32 factor whose L^-1 goes to the kept
-        // per-block store, and the diagonal from the fp32 W (not stored)
+        // per-block store, and the diagonal from the fp32 W, which is stored
         float* L32b = fast ? s->L32 + (int64_t)b0 * bstride : nullptr;
         if (mark_begin(s) != hipSuccess) return fail();
         const hipError_t eg = fast ? launch_gram_blocks32(G, m, d, block, b0, nb, mu, s->A32, s->mp, s->gpart, s->st)
@@ -881,7 +881,7 @@ MFAC_API mfac_status mfac_static_precompute(mfac_static* out, int64_t d, int32_t
         if (ef != hipSuccess) return fail();
         if (mark_end(s, 1) != hipSuccess || mark_begin(s) != hipSuccess) return fail();
         const hipError_t et =
-            fast ? launch_trmm32(L32b, s->mp, bstride, G, m, d, block, b0, nb, lambda, s->diag, nullptr, s->st)
+            fast ? launch_trmm32(L32b, s->mp, bstride, G, m, d, block, b0, nb, lambda, s->diag, s->W, s->st)
                  : launch_trmm_diag(s->Linv, s->mp, bstride, G, m, d, block, b0, nb, lambda, s->diag, s->st);
         if (et != hipSuccess) return fail();
         if (mark_end(s, 2) != hipSuccess) return fail();
@@ -923,24 +923,9 @@ MFAC_API mfac_status mfac_obs_mask(mfac_static s, const float* theta, int64_t ke
     return MFAC_OK;
 }
 
-namespace {
-// Fast mode: W = L^-1 G for every block into the W buffer, once, from the kept
-// fp32 L^-1 (G stays intact for later keep-masks).
-mfac_status ensure_w(mfac_static s) {
-    if (!s->fast || s->w_ready) return MFAC_OK;
-    const int64_t bstride = (int64_t)s->mp * s->mp;
-    HIPCHK(launch_trmm32(s->L32, s->mp, bstride, s->G, s->m, s->d, s->B, 0, s->nblocks, s->lambda, nullptr, s->W,
-                         s->st));
-    s->w_ready = true;
-    return MFAC_OK;
-}
-}  // namespace
-
 MFAC_API mfac_status mfac_static_ihvp(mfac_static s, int32_t n, const float* X, float* Y) {
     if (!s || !X || !Y || n < 1 || n > 4 || !aligned16(X) || !aligned16(Y)) return MFAC_EINVAL;
     const double inv_lam = 1.0 / s->lambda;
-    const mfac_status rc = ensure_w(s);
-    if (rc != MFAC_OK) return rc;
     HIPCHK(launch_static_ihvp(s->W, s->m, s->d, s->B, n, X, (float)inv_lam, inv_lam, Y, s->qpart, s->qcoef, s->st));
     return MFAC_OK;
 }
@@ -948,8 +933,6 @@ MFAC_API mfac_status mfac_static_ihvp(mfac_static s, int32_t n, const float* X, 
 MFAC_API mfac_status mfac_static_element(mfac_static s, int64_t nq, const int64_t* ij, double* out) {
     if (!s || nq < 0 || (nq > 0 && (!ij || !out)) || ((uintptr_t)ij & 7u) || ((uintptr_t)out & 7u))
         return MFAC_EINVAL;
-    const mfac_status rc = ensure_w(s);
-    if (rc != MFAC_OK) return rc;
     HIPCHK(launch_static_element(s->W, s->m, s->d, s->B, nq, ij, s->lambda, out, s->err, s->st));
     return MFAC_OK;
 }
@@ -957,17 +940,6 @@ MFAC_API mfac_status mfac_static_element(mfac_static s, int64_t nq, const int64_
 MFAC_API mfac_status mfac_obs_update(mfac_static s, const float* theta, const uint8_t* keep_mask, float* delta_out) {
     if (!s || !theta || !keep_mask || !delta_out || !aligned4(theta) || !aligned16(delta_out)) return MFAC_EINVAL;
     const double inv_lam = 1.0 / s->lambda;
-    // Fast mode before any query has formed W: W^T W x = G^T L^-T L^-1 G x, from
-    // G and the kept L^-1. Forming W costs 30 ms at d = 4.19M, m = 1024, this
-    // product 1 ms more per call than two passes over W.
-    if (s->fast && !s->w_ready && launch_static_ihvp_factored) {
-        HIPCHK(launch_obs_x(theta, keep_mask, s->diag, s->d, s->xobs, s->st));
-        HIPCHK(launch_static_ihvp_factored(s->G, s->L32, s->mp, (int64_t)s->mp * s->mp, s->m, s->d, s->B, s->xobs,
-                                           (float)-inv_lam, -inv_lam, delta_out, s->qpart, s->qcoef, s->st));
-        return MFAC_OK;
-    }
-    const mfac_status rc = ensure_w(s);
-    if (rc != MFAC_OK) return rc;
     HIPCHK(launch_obs_x(theta, keep_mask, s->diag, s->d, s->xobs, s->st));
     // delta = -F^-1 x = -x / lambda + W^T (W x) / lambda
     HIPCHK(launch_static_ihvp(s->W, s->m, s->d, s->B, 1, s->xobs, (float)-inv_lam, -inv_lam, delta_out, s->qpart,

@@ -144,9 +144,8 @@ hipError_t launch_trmm_diag(const double* Linv, int mp, int64_t bstride, float* 
                             int64_t d, int B, int b0, int nb, double lam, double* diag,
                             hipStream_t st);
 // W_b = Linv_b G_b in fp32 (bf16 parts) for blocks [b0, b0+nb): Linv the fp32 L^-1
-// of each block at batch stride lstride; G is read only. diag (or nullptr):
-// (1 - colsum(W^2)) / lam in fp64 from the fp32 W. Wout (or nullptr): W, row
-// stride d.
+// of each block at batch stride lstride; G is read only. diag: (1 - colsum(W^2)) / lam
+// in fp64 from the fp32 W. Wout: W, row stride d.
 hipError_t launch_trmm32(const float* Linv, int mp, int64_t lstride, const float* G, int m, int64_t d, int B, int b0,
                          int nb, double lam, double* diag, float* Wout, hipStream_t st);
 hipError_t launch_diag_to_f32(const double* diag, int64_t d, float* out, hipStream_t st);
@@ -180,13 +179,6 @@ int64_t static_query_part_doubles(int64_t d, int B, int m);
 // Y = alpha X - W_b^T (pscale W_b X) per block, n <= 4 vectors (row-major, stride d)
 hipError_t launch_static_ihvp(const float* W, int m, int64_t d, int B, int n, const float* X, float alpha,
                               double pscale, float* Y, double* part, double* coef, hipStream_t st);
-// The same for one vector from G and the fp32 L^-1 of every block (fast mode),
-// without W: Y = alpha X - G_b^T (pscale L_b^-T L_b^-1 G_b X). m <= 4096. Weak: a
-// host build of the C ABI may link without it, and then W is formed.
-__attribute__((weak)) hipError_t launch_static_ihvp_factored(const float* G, const float* L32, int mp,
-                                                             int64_t lstride, int m, int64_t d, int B,
-                                                             const float* X, float alpha, double pscale, float* Y,
-                                                             double* part, double* coef, hipStream_t st);
 hipError_t launch_obs_x(const float* theta, const uint8_t* keep, const double* diag, int64_t d, float* x,
                         hipStream_t st);
 hipError_t launch_static_element(const float* W, int m, int64_t d, int B, int64_t nq, const int64_t* ij, double lam,

@@ -162,9 +162,10 @@ __global__ __launch_bounds__(512, 4) void k_trmm_diag(const double* __restrict__
 
 // The same product for the fast static mode, W = L^-1 G_b with fp32 products on
 // the bf16 matrix cores (split_mfma.h), L^-1 the fp32 factor's output. G is only
-// read. W is stored (fp32, row stride d) when Wout is set; the column sums of
-// squares of the fp32 W values are summed in fp64 and give the diagonal when
-// diag is set. A work-group owns a BN-column slice of one block and walks its
+// read. W is stored (fp32, row stride d), and the column sums of squares of its
+// fp32 values, summed in fp64, give the diagonal. (The store costs 1.5 of 30 ms at d =
+// 4.19M, m = 1024; W formed later, for the first query, costs the whole product
+// again.) A work-group owns a BN-column slice of one block and walks its
 // BN-row tiles; waves of WM x WN, 16-deep k-chunks double-buffered in LDS and
 // converted as they are staged, the schedule of k_gram_blocks32. 32 x 32 pieces past row m or column ncol are skipped, and in
 // the diagonal tile a piece stops at its own rows (L^-1 is zero right of them;
@@ -287,11 +288,10 @@ __global__ __launch_bounds__((BN / WM) * (BN / WN) * 64, BN == 128 ? 4 : 2) void
                     const float w = acc[x][y][q];
                     if (row < m) {
                         sqs[y] += (double)w * (double)w;
-                        if (Wout && col < ncol) Wout[(int64_t)row * d + (int64_t)b * B + c0 + col] = w;
+                        if (col < ncol) Wout[(int64_t)row * d + (int64_t)b * B + c0 + col] = w;
                     }
                 }
     }
-    if (!diag) return;
     // column sums of squares: over the two lanes of one column, then over the wr
 #pragma unroll
     for (int y = 0; y < NY; ++y) {

@@ -179,97 +179,6 @@ __global__ __launch_bounds__(256) void k_sq_pass2(const float* __restrict__ W, i
         }
 }
 
-// part[(b * S + s) * m + k] = share s of c_b = L_b^-T (L_b^-1 p_b), p_b = coef[b],
-// for the fast mode's fp32 L_b^-1 (lower triangle; entries right of the
-// diagonal are not read as values). Both products in one read of L_b^-1: a wave
-// takes R rows at a time, z_i = row_i . p across its lanes, and adds z_i row_i
-// to the columns it holds in registers (U quads per lane), in fp64. The waves'
-// columns are added in order; rows go round-robin over the S work-groups of a
-// block. Grid (S, blocks). Bound by reading the lower half of L^-1: 4.3 GB at
-// d = 4.19M, B = 2048, m = 1024, against the 17 GB written and as many MFMA
-// flops as the precompute's W for forming W first (30 ms).
-template <int U, int R>
-__global__ __launch_bounds__(512) void k_lt_l(const float* __restrict__ L32, int mp, int64_t lstride, int m,
-                                              const double* __restrict__ coef, double* __restrict__ part) {
-    constexpr int NW = 8;
-    __shared__ double ps[U * 256], cs[U * 256];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int S = gridDim.x, b = blockIdx.y;
-    const float* __restrict__ L = L32 + (int64_t)b * lstride;
-    for (int k = threadIdx.x; k < U * 256; k += 512) {
-        ps[k] = k < m ? coef[(int64_t)b * m + k] : 0.0;
-        cs[k] = 0.0;
-    }
-    __syncthreads();
-    double c[U][4];
-#pragma unroll
-    for (int u = 0; u < U; ++u) c[u][0] = c[u][1] = c[u][2] = c[u][3] = 0.0;
-    for (int i0 = ((int)blockIdx.x * NW + wave) * R; i0 < m; i0 += S * NW * R) {
-        float4 q[R][U];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (256 * u < i0 + R) {
-                const int k = u * 256 + lane * 4;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    // past mp: a clamped quad, dropped below (k > i)
-                    q[r][u] = ld_stream(L + (int64_t)min(i0 + r, m - 1) * mp + min(k, mp - 4));
-                }
-            }
-        double z[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) z[r] = 0.0;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (256 * u < i0 + R) {
-                const int k = u * 256 + lane * 4;
-                const double2 p0 = *reinterpret_cast<const double2*>(ps + k);
-                const double2 p1 = *reinterpret_cast<const double2*>(ps + k + 2);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = i0 + r;
-                    float4& t = q[r][u];
-                    if (256 * u + 255 > i0)  // the chunk of the diagonal
-                        t = make_float4(k <= i ? t.x : 0.f, k + 1 <= i ? t.y : 0.f, k + 2 <= i ? t.z : 0.f,
-                                        k + 3 <= i ? t.w : 0.f);
-                    z[r] = fma((double)t.x, p0.x, z[r]);
-                    z[r] = fma((double)t.y, p0.y, z[r]);
-                    z[r] = fma((double)t.z, p1.x, z[r]);
-                    z[r] = fma((double)t.w, p1.y, z[r]);
-                }
-            }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-            for (int r = 0; r < R; ++r) z[r] += __shfl_xor(z[r], o, 64);
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (i0 + r >= m) z[r] = 0.0;  // a clamped row past m
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (256 * u < i0 + R) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    c[u][0] = fma((double)q[r][u].x, z[r], c[u][0]);
-                    c[u][1] = fma((double)q[r][u].y, z[r], c[u][1]);
-                    c[u][2] = fma((double)q[r][u].z, z[r], c[u][2]);
-                    c[u][3] = fma((double)q[r][u].w, z[r], c[u][3]);
-                }
-            }
-    }
-    for (int w = 0; w < NW; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) cs[u * 256 + lane * 4 + j] += c[u][j];
-        }
-        __syncthreads();
-    }
-    double* out = part + ((int64_t)b * S + blockIdx.x) * m;
-    for (int k = threadIdx.x; k < m; k += 512) out[k] = cs[k];
-}
-
 // x_j = theta_j / [F^-1]_jj where keep_mask_j == 0, else 0
 __global__ void k_obs_x(const float* __restrict__ theta, const uint8_t* __restrict__ keep,
                         const double* __restrict__ diag, int64_t d, float* __restrict__ x) {
@@ -317,11 +226,10 @@ struct SqCfg {
     static constexpr int RB2 = NV == 2 ? 8 : 4;
 };
 
-// Pass 1 and its reduction: coef[b][i*NV + v] = scale (W_b x_v)_i.
 template <int NV>
-hipError_t sq_pass1_nv(const float* W, int m, int64_t d, int B, const float* X, double scale, double* part,
-                       double* coef, hipStream_t st) {
-    constexpr int U = SqCfg<NV>::U;
+hipError_t sq_ihvp_nv(const float* W, int m, int64_t d, int B, const float* X, float alpha, double pscale, float* Y,
+                      double* part, double* coef, hipStream_t st) {
+    constexpr int U = SqCfg<NV>::U, U2 = SqCfg<NV>::U2, RB2 = SqCfg<NV>::RB2;
     static_assert(256 * U >= 1024, "partials are sized for chunks of at least 1024 columns");
     const int nblocks = (int)(d / B);
     const int cpb = (int)ceil_div(B, 256 * U);
@@ -341,30 +249,18 @@ hipError_t sq_pass1_nv(const float* W, int m, int64_t d, int B, const float* X, 
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)ceil_div(m * NV, 256), nblocks), dim3(256), 0, st, part2,
-                           nseg, m * NV, scale, coef);
+                           nseg, m * NV, pscale, coef);
     } else {
         hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)ceil_div(m * NV, 256), nblocks), dim3(256), 0, st, part,
-                           cpb, m * NV, scale, coef);
+                           cpb, m * NV, pscale, coef);
     }
-    return hipGetLastError();
-}
-
-template <int NV>
-hipError_t sq_pass2_nv(const float* W, int m, int64_t d, int B, const float* X, float alpha, const double* coef,
-                       float* Y, hipStream_t st) {
-    constexpr int U2 = SqCfg<NV>::U2, RB2 = SqCfg<NV>::RB2;
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     const int cpb2 = (int)ceil_div(B, 256 * U2);
-    const int64_t nw = (d / B) * cpb2;
+    const int64_t nw = (int64_t)nblocks * cpb2;
     hipLaunchKernelGGL((k_sq_pass2<NV, U2, RB2>), dim3((unsigned)ceil_div(nw, 4)), dim3(256), 0, st, W, m, d, B, cpb2, nw,
                        coef, X, alpha, Y);
     return hipGetLastError();
-}
-
-template <int NV>
-hipError_t sq_ihvp_nv(const float* W, int m, int64_t d, int B, const float* X, float alpha, double pscale, float* Y,
-                      double* part, double* coef, hipStream_t st) {
-    hipError_t e = sq_pass1_nv<NV>(W, m, d, B, X, pscale, part, coef, st);
-    return e != hipSuccess ? e : sq_pass2_nv<NV>(W, m, d, B, X, alpha, coef, Y, st);
 }
 
 }  // namespace
@@ -383,46 +279,6 @@ hipError_t launch_static_ihvp(const float* W, int m, int64_t d, int B, int n, co
         case 4: return sq_ihvp_nv<4>(W, m, d, B, X, alpha, pscale, Y, part, coef, st);
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_static_ihvp_factored(const float* G, const float* L32, int mp, int64_t lstride, int m, int64_t d,
-                                       int B, const float* X, float alpha, double pscale, float* Y, double* part,
-                                       double* coef, hipStream_t st) {
-    hipError_t e = sq_pass1_nv<1>(G, m, d, B, X, 1.0, part, coef, st);
-    if (e != hipSuccess) return e;
-    // work-groups per block: enough for the chip when there are few blocks, each
-    // with at least 64 rows; the pass-1 partials' room holds 4 ceil(B / 1024) shares
-    const int nblocks = (int)(d / B);
-    int64_t S = ceil_div(512, nblocks);
-    const int64_t room = 4 * ceil_div(B, 1024), rows = ceil_div(m, 64);
-    if (S > room) S = room;
-    if (S > rows) S = rows;
-    // launches over at most 65535 blocks (the grid's second dimension)
-    for (int b0 = 0; b0 < nblocks; b0 += 65535) {
-        const int nb = nblocks - b0 < 65535 ? nblocks - b0 : 65535;
-        const float* L = L32 + (int64_t)b0 * lstride;
-        const double* c = coef + (int64_t)b0 * m;
-        double* o = part + (int64_t)b0 * S * m;
-        const dim3 gr((unsigned)S, (unsigned)nb);
-        if (m <= 256)
-            hipLaunchKernelGGL((k_lt_l<1, 8>), gr, dim3(512), 0, st, L, mp, lstride, m, c, o);
-        else if (m <= 512)
-            hipLaunchKernelGGL((k_lt_l<2, 4>), gr, dim3(512), 0, st, L, mp, lstride, m, c, o);
-        else if (m <= 1024)
-            hipLaunchKernelGGL((k_lt_l<4, 4>), gr, dim3(512), 0, st, L, mp, lstride, m, c, o);
-        else if (m <= 2048)
-            hipLaunchKernelGGL((k_lt_l<8, 2>), gr, dim3(512), 0, st, L, mp, lstride, m, c, o);
-        else if (m <= 4096)
-            hipLaunchKernelGGL((k_lt_l<16, 1>), gr, dim3(512), 0, st, L, mp, lstride, m, c, o);
-        else
-            return hipErrorInvalidValue;
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_sq_reduce, dim3((unsigned)ceil_div(m, 256), nblocks), dim3(256), 0, st, part, (int)S, m,
-                       pscale, coef);
-    e = hipGetLastError();
-    return e != hipSuccess ? e : sq_pass2_nv<1>(G, m, d, B, X, alpha, coef, Y, st);
 }
 
 hipError_t launch_obs_x(const float* theta, const uint8_t* keep, const double* diag, int64_t d, float* x,

@@ -257,12 +257,14 @@ hipError_t launch_gram_blocks32(const float* G, int m, int64_t d, int B, int b0,
     if (gram_blocks32_part_doubles(nb, mp, B)) IN(part, gram_blocks32_part_doubles(nb, mp, B) * 8);
     return launched();
 }
+long trmm32_launches = 0;
 hipError_t launch_trmm32(const float* Linv, int mp, int64_t lstride, const float* G, int m, int64_t d, int B, int b0,
                          int nb, double, double* diag, float* Wout, hipStream_t) {
     IN(Linv, ((int64_t)(nb - 1) * lstride + (int64_t)mp * mp) * 4);
     IN(G, ((int64_t)(m - 1) * d + (int64_t)(b0 + nb) * B) * 4);
-    if (diag) IN(diag + (int64_t)b0 * B, (int64_t)nb * B * 8);
-    if (Wout) IN(Wout, ((int64_t)(m - 1) * d + (int64_t)(b0 + nb) * B) * 4);
+    IN(diag + (int64_t)b0 * B, (int64_t)nb * B * 8);
+    IN(Wout, ((int64_t)(m - 1) * d + (int64_t)(b0 + nb) * B) * 4);
+    ++trmm32_launches;
     return launched();
 }
 int64_t band_work_doubles(int m, int B) { return 64 * (3 * (int64_t)((m + 3) & ~3) + B) + 2 * 6 * 64; }
@@ -561,6 +563,7 @@ void drive_static(int64_t d, int B, int m, bool paged, bool fast = false) {
         CHECK(make(&s, flags) == MFAC_OK);
         const long n_pre = launches - before;
         if (!s) return;
+        const long n_w = mfac::trmm32_launches;  // the fast mode's W is whole after the precompute
         CHECK(mfac_inv_diag(s, diag) == MFAC_OK);
         CHECK(mfac_inv_diag64(s, diag64) == MFAC_OK);
         CHECK(mfac_obs_mask(s, theta, d / 2, scores, mask) == MFAC_OK);
@@ -570,6 +573,7 @@ void drive_static(int64_t d, int B, int m, bool paged, bool fast = false) {
         CHECK(mfac_static_ihvp(s, 5, X, Y) == MFAC_EINVAL);
         CHECK(mfac_static_element(s, 64, ij, out) == MFAC_OK);
         CHECK(mfac_obs_update(s, theta, mask, Y) == MFAC_OK);
+        CHECK(mfac::trmm32_launches == n_w);
         double ms[MFAC_STATIC_NPHASES];
         int64_t cnt[MFAC_STATIC_NPHASES];
         CHECK(mfac_static_trace_read(s, ms, cnt) == MFAC_OK);

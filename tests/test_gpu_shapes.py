@@ -98,13 +98,12 @@ def test_fast_gram_and_w(dev, m, B, nb):
     assert rel_l2(Y, ostatic.ihvp(G.numpy(), wl.lam, B, X.numpy())[0]) < 1e-6
 
 
-# every register width of the factored correction (m <= 256, 512, 1024, 2048,
-# 4096), few blocks (several shares of rows per block) and many
+# m below and above the tiles, up to the fast mode's largest; few blocks and many
 @pytest.mark.parametrize("m,B,nb", [(3, 8, 5), (256, 64, 600), (300, 2048, 2), (511, 1024, 3), (1000, 500, 4),
                                     (1025, 128, 2), (2049, 256, 2), (4096, 64, 2)])
 def test_fast_obs_update_without_and_with_w(dev, m, B, nb):
-    """The OBS correction from G and L^-1, and again from W once a query has
-    formed it. Against the oracle both carry the fp32 factor's rounding
+    """The OBS correction before and after another query. Against the oracle both
+    carry the fp32 factor's rounding
     (bound 4e-6: S's of test_fast_gram_and_w, and theta / diag in fp32)."""
     from paper_2107_03356_amd import StaticBlocks
     say("fast obs_update", m, B, nb)
@@ -123,6 +122,32 @@ def test_fast_obs_update_without_and_with_w(dev, m, B, nb):
     ref = ostatic.obs_update(G.numpy(), wl.lam, B, theta.numpy(), mask.numpy())
     assert rel_l2(d1, ref) < 4e-6
     assert rel_l2(d2, ref) < 4e-6
+
+
+@pytest.mark.parametrize("m,B,nb", [(3, 8, 5), (130, 300, 6), (256, 64, 600)])
+def test_fast_queries_do_not_read_g(dev, m, B, nb):
+    """G may be reused once the precompute (and any keep-mask) is done: the
+    queries answer from the W in the workspace, whatever was called before, and
+    the same call gives the same bits before and after the others."""
+    from paper_2107_03356_amd import StaticBlocks
+    say("fast queries without G", m, B, nb)
+    base = get_workload("static_d4.19m_b2048_m1024")
+    wl = base.scaled(d=B * nb, m=m, block=B, lam=1e-4, scale_d=base.d)
+    gs = GradientStream(wl, seed=m + B)
+    G, theta, X = gs.rows(0, m), gs.theta(), gs.queries(0, 1)
+    Gd = G.to(dev).contiguous()
+    sb = StaticBlocks(Gd, B, wl.lam, fp32=True)
+    mask = (torch.arange(wl.d) % 3 != 0).to(torch.uint8)
+    d1 = sb.obs_update(theta.to(dev), mask.to(dev)).cpu().numpy()
+    Gd.fill_(7.0)
+    d2 = sb.obs_update(theta.to(dev), mask.to(dev)).cpu().numpy()
+    Y = sb.ihvp(X.to(dev)).cpu().numpy()[0]
+    d3 = sb.obs_update(theta.to(dev), mask.to(dev)).cpu().numpy()
+    assert sb.status() == 0
+    np.testing.assert_array_equal(d1, d2)
+    np.testing.assert_array_equal(d1, d3)
+    assert rel_l2(Y, ostatic.ihvp(G.numpy(), wl.lam, B, X.numpy())[0]) < 1e-6
+    assert rel_l2(d1, ostatic.obs_update(G.numpy(), wl.lam, B, theta.numpy(), mask.numpy())) < 4e-6
 
 
 # units of 2048, 1024, 512 and 256 columns in the one-vector passes: fewer units

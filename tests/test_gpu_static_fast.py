@@ -5,7 +5,7 @@ carries fp32 rounding, while the keep-mask must still equal the oracle's bit
 for bit (its band at the cut is recomputed in fp64). Each case checks:
 the diagonal and every score against the oracle (the measured score error
 far below the band's half-width, 1e-5), the mask bit for bit, G left intact,
-and the queries (which form W on first use) against the oracle.
+and the queries (from the W in the workspace) against the oracle.
 """
 
 import numpy as np
@@ -90,7 +90,7 @@ def test_fast_mode_matches_oracle(dev, m, B, nb, lam, batch_cap, monkeypatch):
     sref = omask.scores(theta.numpy(), dref)
     _certificate(scores, sref, keep)
     np.testing.assert_array_equal(mask, omask.keep_mask(sref, keep))
-    # queries form W on first use, from the kept fp32 L^-1
+    # queries from the W that the precompute left in the workspace
     X = GradientStream(wl, seed=42).queries(0, 2)
     Y = sb.ihvp(X.to(dev)).cpu().numpy()
     Yo = ostatic.ihvp(Gn, lam, B, X.numpy())
