@@ -240,13 +240,18 @@ __global__ __launch_bounds__(4 * BT, 4) void k_bgemm(GemmArgs<T> g) {
         const bool idle = mrow0 + wr * 32 >= g.M || ncol0 + wc * HW >= g.N ||
                           ((g.flags & LOWER_ONLY) && I == J && wr * 32 + 31 < wc * HW);
         if (nchunk > 0) load_chunk(klo);
-        // beta C enters as the accumulator's start value (scaled by 1/alpha), so
-        // its loads issue together with the first chunk's
+        // fp64: beta C enters as the accumulator's start value (scaled by 1/alpha),
+        // so its loads issue together with the first chunk's
         // (the test is uniform and outside the loops, so all 32 loads issue
-        // before the first wait)
+        // before the first wait). fp32: the product is summed from zero and C added
+        // once at the end. An accumulator that starts at a diagonal entry of A
+        // (m lambda and more) loses most of the squares taken from it four at a time,
+        // each below its last bit: 1 - lam diag came out low by 1e-7 to 3e-6, now by
+        // 3e-8 to 4e-7 (m = 1024, B = 64 to 4096); no difference in time.
+        constexpr bool C_FIRST = sizeof(T) == 8;
         typename M::acc acc[2][NY];
         const T cs = (T)(g.beta / g.alpha);
-        if (g.beta != 0.0 && !idle && g.nsplit == 1) {
+        if (C_FIRST && g.beta != 0.0 && !idle && g.nsplit == 1) {
     #pragma unroll
             for (int x = 0; x < 2; ++x)
     #pragma unroll
@@ -315,7 +320,12 @@ __global__ __launch_bounds__(4 * BT, 4) void k_bgemm(GemmArgs<T> g) {
     #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = crow(x, r), col = ccol(y);
-                    if (row < g.M && col < g.N) C[(int64_t)(g.cm0 + row) * ld + g.cn0 + col] = (T)g.alpha * acc[x][y][r];
+                    if (row < g.M && col < g.N) {
+                        T* dst = C + (int64_t)(g.cm0 + row) * ld + g.cn0 + col;
+                        T v = (T)g.alpha * acc[x][y][r];
+                        if (!C_FIRST && g.beta != 0.0) v += (T)g.beta * *dst;
+                        *dst = v;
+                    }
                 }
     };
     tile(I0, J0);
