@@ -204,43 +204,59 @@ __global__ __launch_bounds__(512, 4) void k_gram_window(const float* __restrict_
 #undef MFAC_GW_LOAD
 #undef MFAC_GW_STORE
 
-// K[row][col] (both triangles) = sum over splits of the tile partials, in a
-// fixed order; a diagonal tile contributes its lower triangle (mirrored). Bound
-// by reading the partials (~2048 tiles of 128 KB, whatever m is), so every
-// work-group takes only 32 adjacent elements of one tile, eight threads an
-// element, each summing every eighth split with eight loads in flight (the
-// eight sums then added in order): one work-group per tile, each thread walking
-// all splits, took 12.4 ms at m = 256 (3 tiles, 683 splits), 4.7 ms at m = 512.
-// Grid (ntiles, WT * WT / 32).
+// Sum over the splits of one element of the tile partials (src: split 0, `stride`
+// doubles apart), in a fixed order, by TPE threads: 256 / TPE adjacent elements
+// a work-group, thread t taking element t % (256 / TPE). Every thread calls it;
+// the first 256 / TPE hold the result.
+template <int TPE>
+__device__ __forceinline__ double sum_splits(const double* __restrict__ src, int64_t stride, int nsplit, bool use) {
+    constexpr int EL = 256 / TPE;
+    const int el = threadIdx.x % EL, sg = threadIdx.x / EL;
+    double s = 0.0;
+    if (use)
+        for (int k = sg; k < nsplit; k += 8 * TPE) {
+            double q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] = k + TPE * u < nsplit ? src[(int64_t)(k + TPE * u) * stride] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += q[u];
+        }
+    if constexpr (TPE > 1) {
+        __shared__ double red[TPE][EL];
+        red[sg][el] = s;
+        __syncthreads();
+        s = red[0][el];
+#pragma unroll
+        for (int u = 1; u < TPE; ++u) s += red[u][el];
+    }
+    return s;
+}
+
+// Whether one thread an element is enough to fill the chip: eight work-groups per
+// CU and more. Otherwise (few tiles, whose splits are then many) eight threads share
+// an element, each summing every eighth split: one thread walking all splits took
+// 12.4 ms for a window's 3 tiles of 683 splits (one work-group per tile). One
+// against eight threads, 512 blocks of m = 1024 in 2 splits: 1.2 against 6.0 ms;
+// 64 in 8: 0.47 against 1.05; 32 in 16: 0.39 against 0.57; a window of m = 1024
+// (2304 work-groups, 57 splits): no difference.
+inline bool one_thread_sums(int64_t elements) { return elements >= 2048 * 256; }
+
+// K[row][col] (both triangles) = sum over splits of the tile partials; a diagonal
+// tile contributes its lower triangle (mirrored). Bound by reading the partials
+// (~2048 tiles of 128 KB, whatever m is). Grid (ntiles, WT * WT * TPE / 256).
+template <int TPE>
 __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ part, int nsplit,
                                                      int ntiles, int m, double* __restrict__ K) {
-    __shared__ double red[8][32];
+    constexpr int EL = 256 / TPE;
     int ti, tj;
     tile_of(blockIdx.x, ti, tj);
-    const int el = threadIdx.x & 31, sg = threadIdx.x >> 5;
-    const int e = blockIdx.y * 32 + el;
+    const int e = blockIdx.y * EL + threadIdx.x % EL;
     const int rr = e / WT, cc = e % WT;
     const int row = ti * WT + rr, col = tj * WT + cc;
     // diagonal tiles: lower triangle (the rest of the partial is not written)
     const bool use = row < m && col < m && !(ti == tj && rr < cc);
-    double s = 0.0;
-    if (use) {
-        const int64_t stride = (int64_t)ntiles * (WT * WT);
-        const double* src = part + (int64_t)blockIdx.x * (WT * WT) + e;
-        for (int k = sg; k < nsplit; k += 64) {
-            double q[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) q[u] = k + 8 * u < nsplit ? src[(int64_t)(k + 8 * u) * stride] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += q[u];
-        }
-    }
-    red[sg][el] = s;
-    __syncthreads();
-    if (sg == 0 && use) {
-        double v = red[0][el];
-#pragma unroll
-        for (int u = 1; u < 8; ++u) v += red[u][el];
+    const double v = sum_splits<TPE>(part + (int64_t)blockIdx.x * (WT * WT) + e, (int64_t)ntiles * (WT * WT), nsplit, use);
+    if (threadIdx.x < EL && use) {
         K[(int64_t)row * m + col] = v;
         K[(int64_t)col * m + row] = v;
     }
@@ -378,46 +394,35 @@ __global__ __launch_bounds__(512, 4) void k_gram_blocks(const float* __restrict_
 // A_b (lower triangle of every tile the factorization reads) = sum over the
 // column splits of the partial tiles (TS x TS), in a fixed order, plus mu on the
 // diagonal (identity on the padding rows); with accum, the sum is added to A_b
-// instead. As k_gram_reduce: 32 adjacent elements a work-group, eight threads an
-// element (one wide block of m <= 128 rows is a single tile of up to 2048
-// splits). Grid (ntiles, nb, TS * TS / 32).
-template <typename OT, int TS>
+// instead. Summed as in k_gram_reduce: one wide block of m <= 128 rows is a single
+// tile of up to 2048 splits, a batch of 512 blocks of 4096 columns in the fast
+// mode is 5120 tiles of two. One thread an element takes four elements, 256 apart
+// (1.5 -> 1.2 ms there). Grid (ntiles, nb, TS * TS / 1024), or TS * TS / 32 with eight threads.
+template <typename OT, int TS, int TPE>
 __global__ __launch_bounds__(256) void k_gram_blocks_reduce(const double* __restrict__ part, int nsplit, int ntiles,
                                                             int m, double mu, int accum, OT* __restrict__ A,
                                                             int mp) {
-    __shared__ double red[8][32];
+    constexpr int EL = 256 / TPE;
     const int tile = blockIdx.x, bl = blockIdx.y;
     int ti, tj;
     tile_of(tile, ti, tj);
-    const int el = threadIdx.x & 31, sg = threadIdx.x >> 5;
-    const int e = blockIdx.z * 32 + el;
-    const int rr = e / TS, cc = e % TS;
-    const int row = ti * TS + rr, col = tj * TS + cc;
-    const bool use = row < mp && col < mp && !(ti == tj && rr < cc);
-    double s = 0.0;
-    if (use) {
-        const int64_t sstride = (int64_t)ntiles * (TS * TS);
-        const double* src = part + (int64_t)bl * nsplit * sstride + (int64_t)tile * (TS * TS) + e;
-        for (int k = sg; k < nsplit; k += 64) {
-            double q[8];
+    const int64_t sstride = (int64_t)ntiles * (TS * TS);
+    const double* src = part + (int64_t)bl * nsplit * sstride + (int64_t)tile * (TS * TS);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) q[u] = k + 8 * u < nsplit ? src[(int64_t)(k + 8 * u) * sstride] : 0.0;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += q[u];
+    for (int q = 0; q < (TPE == 1 ? 4 : 1); ++q) {
+        const int e = (TPE == 1 ? blockIdx.z * 4 + q : blockIdx.z) * EL + threadIdx.x % EL;
+        const int rr = e / TS, cc = e % TS;
+        const int row = ti * TS + rr, col = tj * TS + cc;
+        const bool use = row < mp && col < mp && !(ti == tj && rr < cc);
+        double v = sum_splits<TPE>(src + e, sstride, nsplit, use);
+        if (threadIdx.x < EL && use) {
+            OT* dst = A + (int64_t)bl * mp * mp + (int64_t)row * mp + col;
+            if (accum)
+                v += (double)*dst;
+            else if (row == col)
+                v += (row < m) ? mu : 1.0;
+            *dst = (OT)v;
         }
-    }
-    red[sg][el] = s;
-    __syncthreads();
-    if (sg == 0 && use) {
-        double v = red[0][el];
-#pragma unroll
-        for (int u = 1; u < 8; ++u) v += red[u][el];
-        OT* dst = A + (int64_t)bl * mp * mp + (int64_t)row * mp + col;
-        if (accum)
-            v += (double)*dst;
-        else if (row == col)
-            v += (row < m) ? mu : 1.0;
-        *dst = (OT)v;
     }
 }
 
@@ -598,7 +603,12 @@ hipError_t launch_gram_window(const float* G, int m, int64_t nslab, double* part
                        sps, part, ntiles);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_reduce, dim3(ntiles, WT * WT / 32), dim3(256), 0, st, part, (int)nsplit, ntiles, m, K);
+    if (one_thread_sums((int64_t)ntiles * (WT * WT)))
+        hipLaunchKernelGGL(k_gram_reduce<1>, dim3(ntiles, WT * WT / 256), dim3(256), 0, st, part, (int)nsplit, ntiles,
+                           m, K);
+    else
+        hipLaunchKernelGGL(k_gram_reduce<8>, dim3(ntiles, WT * WT / 32), dim3(256), 0, st, part, (int)nsplit, ntiles,
+                           m, K);
     return hipGetLastError();
 }
 
@@ -660,6 +670,18 @@ int64_t gram_blocks_part_doubles(int nb, int mp, int B) {
 }
 
 namespace {
+template <typename OT, int TS>
+hipError_t gram_blocks_reduce(const double* part, int ns, int ntiles, int nb, int m, double mu, int accum, OT* A, int mp,
+                              hipStream_t st) {
+    if (one_thread_sums((int64_t)nb * ntiles * (TS * TS)))
+        hipLaunchKernelGGL((k_gram_blocks_reduce<OT, TS, 1>), dim3((unsigned)ntiles, (unsigned)nb, TS * TS / 1024),
+                           dim3(256), 0, st, part, ns, ntiles, m, mu, accum, A, mp);
+    else
+        hipLaunchKernelGGL((k_gram_blocks_reduce<OT, TS, 8>), dim3((unsigned)ntiles, (unsigned)nb, TS * TS / 32),
+                           dim3(256), 0, st, part, ns, ntiles, m, mu, accum, A, mp);
+    return hipGetLastError();
+}
+
 template <int BM, int WM, int WN>
 hipError_t gram_blocks32_tile(const float* G, int m, int64_t d, int B, int b0, int nb, double mu, float* A, int mp,
                               double* part, hipStream_t st) {
@@ -670,9 +692,7 @@ hipError_t gram_blocks32_tile(const float* G, int m, int64_t d, int B, int b0, i
                        B, b0, ntiles, ns, kcols, mu, A, mp, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ns == 1) return e;
-    hipLaunchKernelGGL((k_gram_blocks_reduce<float, BM>), dim3((unsigned)ntiles, (unsigned)nb, BM * BM / 32),
-                       dim3(256), 0, st, part, ns, ntiles, m, mu, 0, A, mp);
-    return hipGetLastError();
+    return gram_blocks_reduce<float, BM>(part, ns, ntiles, nb, m, mu, 0, A, mp, st);
 }
 }  // namespace
 
@@ -691,9 +711,7 @@ hipError_t launch_gram_blocks(const float* G, int m, int64_t d, int B, int b0, i
                        ns, kcols, mu, acc, A, mp, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || ns == 1) return e;
-    hipLaunchKernelGGL((k_gram_blocks_reduce<double, GT>), dim3((unsigned)ntiles, (unsigned)nb, GT * GT / 32),
-                       dim3(256), 0, st, part, ns, ntiles, m, mu, acc, A, mp);
-    return hipGetLastError();
+    return gram_blocks_reduce<double, GT>(part, ns, ntiles, nb, m, mu, acc, A, mp, st);
 }
 
 }  // namespace mfac

@@ -30,8 +30,9 @@ def _stream(d, m, lam, seed, **kw):
 
 
 # one tile with one, a few and many splits of the slab range; a second tile of
-# a single row; three tiles
-@pytest.mark.parametrize("d,m", [(2048, 1), (2049, 127), (150_001, 128), (150_001, 129), (70_000, 256)])
+# a single row; three tiles; 28 and 36 tiles (one thread an element from 32 on)
+@pytest.mark.parametrize("d,m", [(2048, 1), (2049, 127), (150_001, 128), (150_001, 129), (70_000, 256), (6000, 896),
+                                 (6000, 897), (30_000, 897)])
 def test_window_gram_reduction(dev, d, m):
     from paper_2107_03356_amd import Window
     say("window Gram d =", d, "m =", m)
@@ -59,6 +60,18 @@ def test_wide_block_gram_reduction(dev, d, m):
     assert np.max(np.abs(diag / ostatic.inv_diag(G.numpy(), 1e-4, d) - 1.0)) < 1e-11
 
 
+# the same for several blocks in 2 to 4 splits each, on both sides of 32 tiles
+@pytest.mark.parametrize("m,B,nb", [(100, 4100, 31), (100, 8192, 33), (300, 6148, 5), (300, 4096, 6)])
+def test_split_blocks_gram_reduction(dev, m, B, nb):
+    from paper_2107_03356_amd import StaticBlocks
+    say("split blocks m =", m, "B =", B, "nb =", nb)
+    G = _stream(B * nb, m, 1e-4, seed=m + B).window()
+    sb = StaticBlocks(G.to(dev).contiguous(), B, 1e-4)
+    diag = sb.inv_diag(fp64=True).cpu().numpy()
+    assert sb.status() == 0
+    assert np.max(np.abs(diag / ostatic.inv_diag(G.numpy(), 1e-4, B) - 1.0)) < 1e-11
+
+
 # fast mode: m and B on both sides of the 32-row pieces, the 64-row padding, the
 # 128- and 256-row tiles, 16-column chunks in odd number, a split block (B > 2048)
 FAST_SHAPES = [(1, 4, 3), (31, 20, 5), (33, 36, 4), (64, 128, 3), (65, 132, 3), (128, 256, 2), (129, 260, 2),
@@ -67,6 +80,11 @@ FAST_SHAPES = [(1, 4, 3), (31, 20, 5), (33, 36, 4), (64, 128, 3), (65, 132, 3), 
 # batches whose factor runs its large products in 256-tiles: whole tiles, one
 # ragged tile in either direction, two levels of them
 FAST_SHAPES += [(512, 16, 130), (520, 16, 70), (700, 32, 40), (1024, 64, 40), (1100, 32, 36)]
+
+
+# split blocks on both sides of the line between eight threads and one an element
+# (8 tiles of 256, 32 of 128), with padding rows, in 2 to 4 splits
+FAST_SHAPES += [(200, 4100, 7), (200, 4100, 8), (330, 6148, 3), (100, 4096, 31), (100, 4096, 32)]
 
 
 @pytest.mark.parametrize("m,B,nb", FAST_SHAPES)
