@@ -143,6 +143,31 @@ def test_fast_diagonal_is_unbiased(dev, m, B, nb):
     assert abs(mean) < (3.1e-7 if B == 64 else 9e-8)
 
 
+# one row: S_j = g_j^2 / (|g|^2 + lam), so a Gram entry's own error; the 256-tile
+# kernel at |g_i|^2 = m lam
+@pytest.mark.parametrize("m,gain", [(1, 900.0), (200, 1.0)])
+def test_fast_gram_sums_keep_low_bits(dev, m, gain):
+    """The mean signed relative error of S, from sums of 2048 squares.
+
+    The sum is rounded after every 16 columns to either side, A, L^-1 and W once:
+    the mean over 64 blocks (m = 1: 64 Gram entries) stays below one rounding,
+    2^-24 = 6e-8. Accumulating in the bf16 MFMA, which cuts what lies below a
+    larger accumulator's last bits, leaves the sums low by several times that.
+    """
+    from paper_2107_03356_amd import StaticBlocks
+    say("fast Gram sums", m)
+    B, nb, lam = 2048, 64, 1e-3
+    g = torch.Generator().manual_seed(m)
+    G = torch.randn((m, B * nb), generator=g) * float(np.sqrt(gain * m * lam / B))
+    sb = StaticBlocks(G.to(dev).contiguous(), B, lam, fp32=True)
+    S = 1.0 - lam * sb.inv_diag(fp64=True).cpu().numpy()
+    assert sb.status() == 0
+    Sref = 1.0 - lam * ostatic.inv_diag(G.numpy(), lam, B)
+    mean = float(np.mean((S - Sref) / (Sref + 1e-9)))
+    say("mean signed relative error of S", f"{mean:+.1e}")
+    assert abs(mean) < 6e-8
+
+
 # m below and above the tiles, up to the fast mode's largest; few blocks and many
 @pytest.mark.parametrize("m,B,nb", [(3, 8, 5), (256, 64, 600), (300, 2048, 2), (511, 1024, 3), (1000, 500, 4),
                                     (1025, 128, 2), (2049, 256, 2), (4096, 64, 2)])
