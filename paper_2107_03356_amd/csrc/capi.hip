@@ -438,7 +438,7 @@ MFAC_API mfac_status mfac_window_replace(mfac_window w, int32_t slot, const floa
     if (n > 0) al = al && aligned16(X) && aligned16(Y) && (d % 4 == 0);
 
     // small window, no refactor due, no phases to trace: one launch
-    if (n == 0 && y_out && !w->trace && !refactor_due(w) && step_small(w->m, w->nslab) && launch_step_small) {
+    if (n == 0 && y_out && !w->trace && !refactor_due(w) && step_small(w->m, w->nslab)) {
         HIPCHK(launch_step_small(w->G, w->m, d, w->nslab, k, g_new, y_out, al, (double)w->m * w->lambda, w->K, w->Ainv,
                                  w->mp, w->err, w->st));
         w->since_refactor += 1;

@@ -68,15 +68,13 @@ hipError_t launch_pass2_next(const float* G, int m, int64_t d, int64_t nslab, co
                              hipStream_t st);
 
 // A whole sliding step with an O(m^2) slot update (slot k takes g, y = F^-1 g) of
-// a window that step_small() accepts, in one launch. Weak: a host build of the C
-// ABI may link without it, and then the step runs as separate kernels.
+// a window that step_small() accepts, in one launch.
 // The line: one work-group takes 12 us at 65536 entries of 2 to 16 slabs (19 us
 // as one row of 32 slabs) and 19 to 21 us at twice as many, the separate kernels
 // 17 us in either case.
 inline bool step_small(int m, int64_t nslab) { return m <= 64 && nslab <= 16 && (int64_t)m * nslab * SLAB <= 65536; }
-__attribute__((weak)) hipError_t launch_step_small(float* G, int m, int64_t d, int64_t nslab, int k, const float* g,
-                                                   float* y, bool aligned, double mu, double* K, double* Ainv, int mp,
-                                                   int* err, hipStream_t st);
+hipError_t launch_step_small(float* G, int m, int64_t d, int64_t nslab, int k, const float* g, float* y, bool aligned,
+                             double mu, double* K, double* Ainv, int mp, int* err, hipStream_t st);
 
 // ---------------------------------------------------------------- Gram
 // Window Gram: K (m x m, fp64, full symmetric) = sum over slabs of G_s G_s^T,

@@ -199,6 +199,19 @@ hipError_t launch_write_row(float* G, int m, int64_t d, int64_t nslab, int k, co
     CHECK(k >= 0 && k < m);
     return launched();
 }
+long step_small_launches = 0, factor_launches = 0;
+hipError_t launch_step_small(float* G, int m, int64_t d, int64_t nslab, int k, const float* g, float* y, bool, double mu,
+                             double* K, double* Ainv, int mp, int* err, hipStream_t) {
+    IN(G, nslab * m * SLAB * 4);
+    IN(g, d * 4);
+    IN(y, d * 4);
+    IN(K, (int64_t)m * m * 8);
+    IN(Ainv, (int64_t)mp * mp * 8);
+    IN(err, 4);
+    CHECK(step_small(m, nslab) && k >= 0 && k < m && mu > 0.0);
+    ++step_small_launches;
+    return launched();
+}
 hipError_t launch_pass1(const float* G, int m, int64_t d, int64_t nslab, int nv, const VecIn& vin, bool,
                         double* part, Pass1Grid* grid, hipStream_t) {
     IN(G, nslab * m * SLAB * 4);
@@ -303,6 +316,7 @@ hipError_t launch_factor_invert(double* A, double* Linv, int mp, int nbatch, int
     if (part) IN(part, part_elems * 8);
     // one matrix (the refactor, the one-block precompute) brings room for its split-K segments
     if (nbatch == 1 && mp > 128) CHECK(part && part_elems >= splitk_part_doubles(mp));
+    ++factor_launches;
     CHECK(mp % NB == 0);
     return launched();
 }
@@ -529,6 +543,67 @@ void drive_window(int64_t d, int m, int q) {
     CHECK(mfac_window_destroy(w0) == MFAC_OK);
 }
 
+// The one-launch step of a small window: head, step count and refactor schedule
+// as in the separate kernels, which take over for a refactor, extra queries, no
+// output, tracing and a window just past its size; a failed launch changes nothing.
+void drive_step_small(int64_t d, int m, bool small) {
+    fake_reset();
+    const size_t sb = mfac_window_storage_bytes(d, m), wb = mfac_window_workspace_bytes(d, m, 1);
+    void* storage = fake_alloc(sb, "storage");
+    void* ws = fake_alloc(wb, "workspace");
+    float* g = (float*)fake_alloc((size_t)d * 4 + 16, "g");
+    float* y = (float*)fake_alloc((size_t)d * 4 + 16, "y");
+    float* X = (float*)fake_alloc((size_t)d * 4, "X");
+    float* Y = (float*)fake_alloc((size_t)d * 4, "Y");
+    CHECK(mfac::step_small(m, (d + mfac::SLAB - 1) / mfac::SLAB) == small);
+    mfac_window w = nullptr;
+    CHECK(mfac_window_init(&w, d, m, 1e-3, 1, storage, sb, ws, wb, nullptr, ST) == MFAC_OK);
+    if (!w) return;
+    int32_t head = -1, head0 = 0;
+    int64_t steps = -1, steps0 = 0;
+    auto at = [&](int32_t h, int64_t s) { CHECK(mfac_window_info(w, &head, &steps) == MFAC_OK && head == h && steps == s); };
+    const long one = small ? 1 : 0;
+    // period 3: every third replace refactors, whichever kernels ran in between
+    CHECK(mfac_window_set_refactor_period(w, 3) == MFAC_OK);
+    for (int t = 0; t < 7; ++t) {
+        const long ns = mfac::step_small_launches, nf = mfac::factor_launches;
+        const bool query = t == 4;
+        CHECK(mfac_window_replace(w, -1, g + (t & 1), y, query ? 1 : 0, query ? X : nullptr, query ? Y : nullptr) == MFAC_OK);
+        CHECK(mfac::factor_launches - nf == (t % 3 == 2 ? 1 : 0));
+        CHECK(mfac::step_small_launches - ns == (t % 3 == 2 || query ? 0 : one));
+        at((t + 1) % m, t + 1);
+    }
+    CHECK(mfac_window_set_refactor_period(w, 1 << 20) == MFAC_OK);
+    CHECK(mfac_window_info(w, &head0, &steps0) == MFAC_OK);
+    // a slot given: the head stays
+    long ns = mfac::step_small_launches;
+    CHECK(mfac_window_replace(w, m - 1, g, y, 0, nullptr, nullptr) == MFAC_OK);
+    CHECK(mfac::step_small_launches - ns == one);
+    at(head0, steps0 + 1);
+    // a failed launch: head, steps and schedule unchanged
+    fail_at = launches + 1;
+    CHECK(mfac_window_replace(w, -1, g, y, 0, nullptr, nullptr) == MFAC_EHIP);
+    fail_at = -1;
+    at(head0, steps0 + 1);
+    // refused arguments launch nothing
+    ns = launches;
+    CHECK(mfac_window_replace(w, -1, nullptr, y, 0, nullptr, nullptr) == MFAC_EINVAL);
+    CHECK(mfac_window_replace(w, m, g, y, 0, nullptr, nullptr) == MFAC_EINVAL);
+    CHECK(mfac_window_replace(w, -1, g, (float*)((char*)y + 2), 0, nullptr, nullptr) == MFAC_EINVAL);
+    CHECK(launches == ns);
+    // no output, tracing, policy 0: the separate kernels
+    ns = mfac::step_small_launches;
+    CHECK(mfac_window_replace(w, -1, g, nullptr, 0, nullptr, nullptr) == MFAC_OK);
+    CHECK(mfac_window_trace(w, 1) == MFAC_OK);
+    CHECK(mfac_window_replace(w, -1, g, y, 0, nullptr, nullptr) == MFAC_OK);
+    CHECK(mfac_window_trace(w, 0) == MFAC_OK);
+    CHECK(mfac_window_set_refactor_period(w, 0) == MFAC_OK);
+    CHECK(mfac_window_replace(w, -1, g, y, 0, nullptr, nullptr) == MFAC_OK);
+    CHECK(mfac::step_small_launches == ns);
+    at((head0 + 3) % m, steps0 + 4);
+    CHECK(mfac_window_destroy(w) == MFAC_OK);
+}
+
 void drive_static(int64_t d, int B, int m, bool paged, bool fast = false) {
     fake_reset();
     mfac_static s0_unused = nullptr;
@@ -602,6 +677,11 @@ int main() {
         drive_window(3 * 2048 + 5, 70, q);
         drive_window(1000, 4081, 0);
     }
+    drive_step_small(4096, 16, true);
+    drive_step_small(5, 32, true);
+    drive_step_small(5, 33, false);
+    drive_step_small(16 * 2048, 2, true);
+    drive_step_small(16 * 2048 + 1, 1, false);
     drive_static(4096, 256, 64, false);
     drive_static(8192, 8192, 100, false);    // one wide block: split Gram
     drive_static(3000, 100, 300, false);     // m > B
