@@ -69,10 +69,13 @@ hipError_t launch_pass2_next(const float* G, int m, int64_t d, int64_t nslab, co
 
 // A whole sliding step with an O(m^2) slot update (slot k takes g, y = F^-1 g) of
 // a window that step_small() accepts, in one launch.
-// The line: one work-group takes 12 us at 65536 entries of 2 to 16 slabs (19 us
-// as one row of 32 slabs) and 19 to 21 us at twice as many, the separate kernels
-// 17 us in either case.
-inline bool step_small(int m, int64_t nslab) { return m <= 64 && nslab <= 16 && (int64_t)m * nslab * SLAB <= 65536; }
+// The line, rows times slabs (2048 entries each), in steps queued behind other
+// work: one launch takes 5 to 15 us up to 32 of them, 16 to 17 at 48 and 19 to 23 at
+// 64, a row of 32 slabs 19; the separate kernels 17 to 18 in all of these. (Steps
+// entered into an empty queue are bound by the host's six launches there, 22 to 26
+// us.)
+constexpr int SMALL_MAX_ROWSLABS = 32;
+inline bool step_small(int m, int64_t nslab) { return nslab <= 16 && m * nslab <= SMALL_MAX_ROWSLABS; }
 hipError_t launch_step_small(float* G, int m, int64_t d, int64_t nslab, int k, const float* g, float* y, bool aligned,
                              double mu, double* K, double* Ainv, int mp, int* err, hipStream_t st);
 

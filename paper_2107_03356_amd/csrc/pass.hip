@@ -550,13 +550,14 @@ __global__ __launch_bounds__(256) void k_write_row(float* __restrict__ G, int m,
     *reinterpret_cast<float4*>(G + slab * (int64_t)m * SLAB + (int64_t)k * SLAB + (j - slab * SLAB)) = v;
 }
 
-// A whole sliding step of a small window (m <= 64) in one work-group: the new
-// row and its Gram column, the slot update of Ainv, its new column k as the
-// coefficients, and y. Separate kernels run 2 to 5 us each on such a window,
-// nearly all of it launch and latency (a step at d = 4096, m = 16: six launches
-// 22 us, this 12 us). The order of the m x m arithmetic is that of k_inv_gemv and
+// A whole sliding step of a small window (step_small: at most 32 rows) in one
+// work-group: the new row and its Gram column, the slot update of Ainv, its new
+// column k as the coefficients, and y. Separate kernels run 2 to 5 us each on such a
+// window, nearly all of it launch and latency (a step at d = 4096, m = 16: six
+// launches 22 to 26 us one after another, 18.5 us queued behind other work; this
+// 11.6 us either way). The order of the m x m arithmetic is that of k_inv_gemv and
 // k_inv_update_coef except for the order of the sums; every sum is fp64.
-constexpr int SMALL_M = 64, SMALL_T = 1024, SMALL_W = SMALL_T / 64;
+constexpr int SMALL_M = SMALL_MAX_ROWSLABS, SMALL_T = 1024, SMALL_W = SMALL_T / 64;
 
 __global__ __launch_bounds__(SMALL_T) void k_step_small(float* __restrict__ G, int m, int64_t d, int ncolpad, int k,
                                                         const float* __restrict__ g, float* __restrict__ y, int aligned,
@@ -565,8 +566,10 @@ __global__ __launch_bounds__(SMALL_T) void k_step_small(float* __restrict__ G, i
     __shared__ double Ai[SMALL_M][SMALL_M + 1];
     __shared__ double part[SMALL_M + SMALL_W], p[SMALL_M], z[SMALL_M], w[SMALL_M], v[SMALL_M], cf[SMALL_M];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int e = tid; e < SMALL_M * SMALL_M; e += SMALL_T)
-        if ((e >> 6) < m) Ai[e >> 6][e & 63] = Ainv[(int64_t)(e >> 6) * mp + (e & 63)];
+    // one entry (er, ec) of Ainv per thread
+    static_assert(SMALL_M * SMALL_M == SMALL_T, "one thread per entry");
+    const int er = tid / SMALL_M, ec = tid % SMALL_M;
+    if (er < m) Ai[er][ec] = Ainv[(int64_t)er * mp + ec];
     // Gram column: tasks of one row and one of nseg column ranges per wave
     const int nseg = m >= SMALL_W ? 1 : SMALL_W / m;
     const int nq = ncolpad / 256;  // wave-wide quads per row
@@ -600,16 +603,12 @@ __global__ __launch_bounds__(SMALL_T) void k_step_small(float* __restrict__ G, i
         if (!isfinite(s)) atomicOr(err, 1);
     }
     __syncthreads();
-    // z = Ainv b (b = p off slot k, 0 at k): 16 threads per row
+    // z = Ainv b (b = p off slot k, 0 at k)
     {
-        const int i = tid >> 4, c = tid & 15;
-        double s = 0.0;
-        if (i < m)
-            for (int j = c; j < m; j += 16)
-                if (j != k) s += Ai[i][j] * p[j];
+        double s = er < m && ec < m && ec != k ? Ai[er][ec] * p[ec] : 0.0;
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (i < m && c == 0) z[i] = s;
+        for (int o = SMALL_M / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (er < m && ec == 0) z[er] = s;
     }
     __syncthreads();
     const double t = v[k], r = z[k] / t;
@@ -622,16 +621,13 @@ __global__ __launch_bounds__(SMALL_T) void k_step_small(float* __restrict__ G, i
     if (tid < m) w[tid] = z[tid] - v[tid] * r - (tid == k ? 1.0 : 0.0);
     __syncthreads();
     const double it = 1.0 / t, is = 1.0 / s;
-    for (int e = tid; e < SMALL_M * SMALL_M; e += SMALL_T) {
-        const int i = e >> 6, j = e & 63;
-        if (i < m && j < m) {
-            const double a = Ai[i][j] - v[i] * v[j] * it + w[i] * w[j] * is;
-            Ainv[(int64_t)i * mp + j] = a;
-            if (j == k) {
-                const double c = a * -(double)m;
-                if (!isfinite(c)) atomicOr(err, 4);
-                cf[i] = c;
-            }
+    if (er < m && ec < m) {
+        const double a = Ai[er][ec] - v[er] * v[ec] * it + w[er] * w[ec] * is;
+        Ainv[(int64_t)er * mp + ec] = a;
+        if (ec == k) {
+            const double c = a * -(double)m;
+            if (!isfinite(c)) atomicOr(err, 4);
+            cf[er] = c;
         }
     }
     __syncthreads();

@@ -271,9 +271,10 @@ def test_keep_mask_selection(dev, d, kind, fast):
 
 
 # the one-launch step of small windows: rows in 8 column ranges, rows that 16
-# waves do not divide, the largest windows it takes and the first it does not, vectors off 16-byte alignment
+# waves do not divide, the largest windows it takes (32 rows times slabs) and the
+# first it does not, vectors off 16-byte alignment
 @pytest.mark.parametrize("d,m,off", [(32_768, 2, 0), (40_000, 1, 0), (5, 32, 1), (5, 64, 1), (2049, 15, 0), (2048, 32, 3), (4095, 16, 1),
-                                     (4096, 17, 0)])
+                                     (4096, 17, 0), (2048, 33, 0), (2048, 31, 0), (10_000, 6, 2), (10_241, 6, 0)])
 def test_small_window_step(dev, d, m, off):
     from paper_2107_03356_amd import Window
     say("small window d =", d, "m =", m, "offset", off)
