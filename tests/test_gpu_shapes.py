@@ -78,8 +78,8 @@ FAST_SHAPES = [(1, 4, 3), (31, 20, 5), (33, 36, 4), (64, 128, 3), (65, 132, 3), 
                (255, 300, 2), (256, 256, 2), (257, 512, 2), (320, 1040, 2), (513, 2048, 1), (200, 2052, 1),
                (130, 4100, 2)]
 # batches whose factor runs its large products in 256-tiles: whole tiles, one
-# ragged tile in either direction, two levels of them
-FAST_SHAPES += [(512, 16, 130), (520, 16, 70), (700, 32, 40), (1024, 64, 40), (1100, 32, 36)]
+# ragged tile in either direction, two levels of them (512 and 256 of m = 1024)
+FAST_SHAPES += [(512, 16, 130), (520, 16, 70), (700, 32, 40), (1024, 64, 40), (1100, 32, 36), (1024, 16, 130)]
 
 
 # split blocks on both sides of the line between eight threads and one an element
@@ -166,6 +166,38 @@ def test_fast_gram_sums_keep_low_bits(dev, m, gain):
     mean = float(np.mean((S - Sref) / (Sref + 1e-9)))
     say("mean signed relative error of S", f"{mean:+.1e}")
     assert abs(mean) < 6e-8
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf"), 3.4e38])
+@pytest.mark.parametrize("m,B", [(20, 36), (300, 256)])
+def test_fast_bad_block_is_reported_and_alone(dev, m, B, bad):
+    """A value that is not finite, or whose square is not (3.4e38 also rounds to
+    infinity as bf16), is reported; the other blocks' results are what they are
+    without it. Columns of zeros and of values whose low parts are subnormal as
+    bf16 next to it change nothing: their S is 0 to fp64."""
+    from paper_2107_03356_amd import MFAC_ENONFINITE, StaticBlocks
+    say("fast bad block", m, B, bad)
+    nb, lam = 5, 1e-3
+    g = torch.Generator().manual_seed(m)
+    G = torch.randn((m, B * nb), generator=g) * 0.01
+    G[:, 3 * B] = 0.0
+    G[:, 3 * B + 1] = 1e-38
+    G[:, 3 * B + 2] = -3e-41
+    X = torch.randn((1, B * nb), generator=g)
+    good = StaticBlocks(G.to(dev).contiguous(), B, lam, fp32=True)
+    dg, Yg = good.inv_diag(fp64=True).cpu().numpy(), good.ihvp(X.to(dev)).cpu().numpy()[0]
+    assert good.status() == 0
+    dref = ostatic.inv_diag(G.numpy(), lam, B)
+    assert np.max(np.abs(dg / dref - 1.0)) < 1e-6
+    np.testing.assert_allclose(dg[3 * B:3 * B + 3], 1.0 / lam, rtol=1e-15)
+    assert rel_l2(Yg, ostatic.ihvp(G.numpy(), lam, B, X.numpy())[0]) < 1e-6
+    G[m // 2, 2 * B + 5] = bad
+    sb = StaticBlocks(G.to(dev).contiguous(), B, lam, fp32=True)
+    d, Y = sb.inv_diag(fp64=True).cpu().numpy(), sb.ihvp(X.to(dev)).cpu().numpy()[0]
+    assert sb.status() == MFAC_ENONFINITE
+    others = np.r_[0:2 * B, 3 * B:5 * B]
+    np.testing.assert_array_equal(d[others], dg[others])
+    np.testing.assert_array_equal(Y[others], Yg[others])
 
 
 # m below and above the tiles, up to the fast mode's largest; few blocks and many
@@ -303,3 +335,29 @@ def test_small_window_step(dev, d, m, off):
         assert win.status() == 0
         assert float(ybuf[off + d]) == 7.0 and (off == 0 or float(ybuf[off - 1]) == 7.0)
     np.testing.assert_array_equal(win.get_rows(0, 1).cpu().numpy()[0], orc.G[0].astype(np.float32))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf"), 1e30])
+@pytest.mark.parametrize("d,m", [(4096, 16), (300, 3)])
+def test_small_window_step_reports_bad_gradients(dev, d, m, bad):
+    """A gradient that is not finite is reported by the one-launch step; a window
+    whose bad row is overwritten and rebuilt works on. 1e30 is finite (its square
+    is summed in fp64) and reported by neither path."""
+    from paper_2107_03356_amd import MFAC_ENONFINITE, Window
+    say("small window, bad gradient", d, m, bad)
+    gs = _stream(d, m, 1e-3, seed=d)
+    win, orc = Window(d, m, 1e-3, device=dev), WindowOracle(d, m, 1e-3)
+    for t in range(m):
+        g = gs.row(t)
+        assert rel_l2(win.replace(g.to(dev)).cpu().numpy(), orc.slide(g.numpy())) < F32_TOL
+    g = gs.row(m).to(dev)
+    g[d // 3] = bad
+    win.replace(g)
+    assert win.status() == (0 if bad == 1e30 else MFAC_ENONFINITE)
+    win.set_rows(0, gs.row(m + 1)[None].to(dev))   # the bad row was slot 0
+    win.rebuild()
+    assert win.status() == 0
+    rows = np.stack([gs.row(m + 1).numpy()] + [gs.row(t).numpy() for t in range(1, m)])
+    orc = WindowOracle(d, m, 1e-3, G0=rows)
+    x = gs.queries(0, 1)
+    assert rel_l2(win.ihvp(x.to(dev)).cpu().numpy()[0], orc.ihvp(x.numpy())[0]) < F32_TOL
