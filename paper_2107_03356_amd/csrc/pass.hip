@@ -309,10 +309,11 @@ __global__ __launch_bounds__(256) void k_pass2(const float* __restrict__ G, int 
 }
 
 // Pass 2 for one vector, y = alpha x - G^T coef, m <= 4096. A unit is 256 U
-// columns of a slab; work-group b takes units b, b + gridDim.x, ... from the
-// last one down (pass 1 went from the first up, and the 256 MB memory-side cache
-// still holds part of what it read last: 120 -> 101 us for a 553 MB window, no
-// change at 1 GB). Wave w folds rows w, w + 4, ... over the unit's width with RB =
+// columns of a slab; work-group b takes units b, b + gridDim.x, ..., narrow units
+// from the last one down (pass 1 went from the first up, and the 256 MB memory-side
+// cache still holds part of what it read last: 120 -> 101 us for a 553 MB window),
+// whole slabs from the first up (down, 3% slower where the last round is partial:
+// 1418 against 1370 us at m = 1024, d = 2.26M). Wave w folds rows w, w + 4, ... over the unit's width with RB =
 // 8 / U rows in flight, loading a row's successor as soon as it is folded and
 // the next unit's first rows before the unit's reduction. Rows past m are
 // re-reads of row m - 1 with coefficient 0: a branch around a load would make
@@ -325,6 +326,12 @@ struct RowUnits {
     static constexpr int RB = 8 / U;        // rows in flight per wave
     static constexpr int W = 256 * U;       // columns of a unit
     static constexpr int PER = SLAB / W;    // units per slab
+    // Whole slabs keep the wave number per lane: known to be uniform, the compiler
+    // waits for a row's successor before the row's arithmetic instead of behind it
+    // (a unit 1 to 2 us slower: 7% at m = 100, d = 1M).
+    static __device__ __forceinline__ int wave_of(int tid) {
+        return U == 8 ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
+    }
     // row 0 of a unit
     static __device__ __forceinline__ const float* base(const float* __restrict__ G, int m, int64_t unit) {
         const int64_t s = unit / PER;
@@ -358,7 +365,10 @@ __device__ __forceinline__ void RowUnits<U>::reduce(double* __restrict__ rb, con
     }
     lds_barrier();
     // wave w adds columns [64 U w, 64 U (w + 1)) of the unit
-    for (int c = lane * 4; c < 64 * U; c += 256) {
+#pragma unroll
+    for (int h = 0; h < (64 * U + 255) / 256; ++h) {
+        const int c = h * 256 + lane * 4;
+        if (64 * U < 256 && c >= 64 * U) continue;
         const int col = wave * 64 * U + c;
         double sum[4];
 #pragma unroll
@@ -381,18 +391,21 @@ __global__ __launch_bounds__(256) void k_pass2_rows(const float* __restrict__ G,
     double* red = sh + mr;  // [2][4][W]
     for (int t = threadIdx.x; t < mr; t += 256) cl[t] = t < m ? coef[t] : 0.0;
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = RU::wave_of(threadIdx.x);
     const float alpha = vout.alpha[0];
     const float* __restrict__ x = vout.x[0];
     float* __restrict__ y = vout.y[0];
     float4 g[RB][U];
-    int64_t s = nunit - 1 - (int64_t)blockIdx.x;  // grid <= nunit
+    constexpr bool DOWN = U < 8;
+    const int64_t step = DOWN ? -(int64_t)gridDim.x : (int64_t)gridDim.x;
+    int64_t s = DOWN ? nunit - 1 - (int64_t)blockIdx.x : (int64_t)blockIdx.x;  // grid <= nunit
     const float* p = RU::base(G, m, s);
 #pragma unroll
     for (int r = 0; r < RB; ++r) RU::load(g[r], p, min(wave + 4 * r, m - 1), lane);
-    for (int t = 0; s >= 0; s -= gridDim.x, ++t) {
+    for (int t = 0; s >= 0 && s < nunit; s += step, ++t) {
         // the last unit loads its own first rows again
-        const float* pn = s >= gridDim.x ? RU::base(G, m, s - gridDim.x) : p;
+        const bool next = s + step >= 0 && s + step < nunit;
+        const float* pn = next ? RU::base(G, m, s + step) : p;
         double acc[U][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.0;
@@ -406,14 +419,18 @@ __global__ __launch_bounds__(256) void k_pass2_rows(const float* __restrict__ G,
             }
         };
         if constexpr (RB == 1) {
-            // one row in flight: every wait is for all loads anyway, and the
-            // branches are cheaper than the selects (2% at d = 1M, m = 256)
+            // one row in flight, its successor's loads issued before its arithmetic (in
+            // one place: with a load per case the arithmetic waits for them, 7% at
+            // m = 60, d = 1M; a branch around them is cheaper than loading the last
+            // unit's first rows again, 2% at d = 1M, m = 256)
             for (int i = wave; i < m; i += 4) {
-                fold(g[0], cl[i]);
-                if (i + 4 < m)
-                    RU::load(g[0], p, i + 4, lane);
-                else if (s >= gridDim.x)
-                    RU::load(g[0], pn, wave, lane);
+                float4 q[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) q[u] = g[0][u];
+                const bool more = i + 4 < m;
+                const float* pl = (more ? p : pn) + (int64_t)(more ? i + 4 : wave) * SLAB;
+                if (more || next) RU::load(g[0], pl, 0, lane);
+                fold(q, cl[i]);
             }
         } else {
             for (int i0 = wave; i0 < mr; i0 += 4 * RB) {
@@ -473,14 +490,15 @@ __global__ __launch_bounds__(256) void k_pass2_next(const float* __restrict__ G,
         rs[t] = 0.0;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, wave = RU::wave_of(threadIdx.x);
     float4 g[RB][U], gv[U];
     int64_t s = blockIdx.x;  // grid <= nunit
     const float* p = RU::base(G, m, s);
 #pragma unroll
     for (int r = 0; r < RB; ++r) RU::load(g[r], p, min(wave + 4 * r, m - 1), lane);
     for (int t = 0; s < nunit; s += gridDim.x, ++t) {
-        const float* pn = s + gridDim.x < nunit ? RU::base(G, m, s + gridDim.x) : p;
+        const bool next = s + gridDim.x < nunit;
+        const float* pn = next ? RU::base(G, m, s + gridDim.x) : p;
 #pragma unroll
         for (int u = 0; u < U; ++u) gv[u] = ld4(gn, s * RU::W + u * 256 + lane * 4, d, aligned);
         double acc[U][4];
@@ -511,18 +529,25 @@ __global__ __launch_bounds__(256) void k_pass2_next(const float* __restrict__ G,
 #pragma unroll
                         for (int u = 0; u < U; ++u) dv = dot4d(gr[u], gv[u], dv);
                     }
-                    // formed here, not at the reduction with all eight rows kept
-                    asm volatile("" : "+v"(dv));
-                    const int il = i + 4 * RB;
-                    const bool more = RB > 1 ? il - wave - 4 * (r % RB) < mr : il < m;  // a further round of rows
-                    RU::load(gr, more ? p : pn, min(more ? il : wave + 4 * (r % RB), m - 1), lane);
+                    if constexpr (RB == 1) {
+                        if (i + 4 < m)
+                            RU::load(gr, p, i + 4, lane);
+                        else if (next)
+                            RU::load(gr, pn, wave, lane);
+                    } else {
+                        // formed here, not at the reduction with all eight rows kept
+                        asm volatile("" : "+v"(dv));
+                        const int il = i + 4 * RB;
+                        const bool more = il - wave - 4 * (r % RB) < mr;  // a further round of rows
+                        RU::load(gr, more ? p : pn, min(more ? il : wave + 4 * (r % RB), m - 1), lane);
+                    }
                 }
                 sv[r] = dv;
             }
             int idx;
             bool writer;
             const double tot = wave_reduce_many<PASS21_RB>(sv, lane, idx, writer);
-            if (writer) rs[i0 + 4 * idx] += tot;  // past m: never read
+            if (writer && (RB > 1 || i0 + 4 * idx < m)) rs[i0 + 4 * idx] += tot;  // past m: never read
         }
         p = pn;
         RU::reduce(red + (t & 1) * 4 * RU::W, acc, wave, lane, [&](int col, const double (&sum)[4]) {
@@ -700,19 +725,40 @@ inline Pass1Grid pass1_grid(int m, int nv, int64_t nchunk, int target, int round
     return best;
 }
 
-// Width of the units of k_pass2_rows / k_pass2_next: the widest of 2048, 1024,
-// 512 and 256 columns whose rounds over the grid are within 3% of the least.
-// Whole slabs leave most of the chip idle where they are fewer than the
-// work-groups or just more than a multiple of them.
-inline int row_unit(int64_t d) {
-    int64_t least = 0;
-    for (int u = 8; u >= 1; u /= 2) {
-        const int64_t c = ceil_div(ceil_div(d, 256 * u), PASS2_ROWS_GRID) * u;
-        if (least == 0 || c < least) least = c;
+// Width of the units of k_pass2_rows / k_pass2_next (fused): 256 u columns, u = 8,
+// 4, 2 or 1. Whole slabs (u = 8) leave most of the chip idle where they are fewer
+// than the work-groups or just more than a multiple of them; narrow units have
+// their fixed part (partials through LDS, the barrier, x and y) more often, take the
+// rows in rounds of 4 RB (32 in the fused pass; rows past m are read from the cache,
+// at half the cost) and stream a little slower. Cost of a width, in pieces of a row
+// and 256 columns: the rounds over the grid, the last one counted 0.7 + 0.3 f^4 for
+// the fraction f of work-groups in it (few work-groups run 1.4 times as fast as all
+// of them; 0.68, 0.73, 0.76 and 0.82 measured at f = 0.06, 0.34, 0.52 and 0.77), times
+// a unit's pieces and its fixed part, times what a piece costs against whole slabs
+// where every width fills its rounds (d = 1,048,576). Over m = 5 to 1024 and d =
+// 30,000 to 11.2M (one vector, and fused) this takes at most a few percent more than
+// whole slabs, and down to a sixth of their time. By the rounds alone the narrow
+// units were also taken where they lose: 34 against 14 us at m = 5, d = 1.5M, 150
+// against 127 at m = 512, d = 400,001, 898 against 855 at m = 1024, d = 1.5M.
+inline int row_unit(int m, int64_t d, bool fused) {
+    static const struct {
+        int u;
+        double fixed[2], piece[2];  // one vector, fused
+    } W[4] = {{8, {32, 100}, {1.0, 1.0}}, {4, {20, 70}, {1.02, 1.03}}, {2, {10, 20}, {1.1, 1.1}}, {1, {6, 10}, {1.12, 1.08}}};
+    int best = 8;
+    double best_cost = 0.0;
+    for (const auto& w : W) {
+        const int64_t n = ceil_div(d, 256 * w.u);
+        const double rows = w.u == 8 ? round_up(m, 4) : 0.5 * (m + round_up(m, fused ? 32 : 32 / w.u));
+        const double f = (double)(n % PASS2_ROWS_GRID) / PASS2_ROWS_GRID;
+        const double rounds = (double)(n / PASS2_ROWS_GRID) + (f > 0.0 ? 0.7 + 0.3 * f * f * f * f : 0.0);
+        const double cost = rounds * (w.u * rows + w.fixed[fused]) * w.piece[fused];
+        if (w.u == 8 || cost < best_cost) {
+            best = w.u;
+            best_cost = cost;
+        }
     }
-    for (int u = 8; u > 1; u /= 2)
-        if (ceil_div(ceil_div(d, 256 * u), PASS2_ROWS_GRID) * u * 100 <= least * 103) return u;
-    return 1;
+    return best;
 }
 
 template <int NV>
@@ -777,7 +823,7 @@ hipError_t pass2_nv(const float* G, int m, int64_t d, int64_t nslab, const doubl
                     const VecOut& vout, bool aligned, hipStream_t st) {
     if constexpr (NV == 1) {
         if (m <= PASS2_ROWS_MAX_M) {
-            switch (row_unit(d)) {
+            switch (row_unit(m, d, false)) {
                 case 8: return pass2_rows<8>(G, m, d, coef, vout, aligned, st);
                 case 4: return pass2_rows<4>(G, m, d, coef, vout, aligned, st);
                 case 2: return pass2_rows<2>(G, m, d, coef, vout, aligned, st);
@@ -865,7 +911,7 @@ hipError_t launch_pass2_next(const float* G, int m, int64_t d, int64_t nslab, co
                              const float* gn, int knext, bool aligned, double* part, Pass1Grid* grid_out,
                              hipStream_t st) {
     if (m > PASS21_MAX_M) return hipErrorInvalidValue;
-    switch (row_unit(d)) {
+    switch (row_unit(m, d, true)) {
         case 8: return pass2_next<8>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);
         case 4: return pass2_next<4>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);
         case 2: return pass2_next<2>(G, m, d, coef, y, gn, knext, aligned, part, grid_out, st);

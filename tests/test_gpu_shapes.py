@@ -257,7 +257,8 @@ def test_fast_queries_do_not_read_g(dev, m, B, nb):
 # at the rows in flight, and rows that no round of the pass divides; one to many
 # row groups in pass 1
 @pytest.mark.parametrize("d,m", [(1, 1), (255, 3), (2049, 33), (66_001, 31), (131_073, 65), (269_722, 40),
-                                 (525_000, 17), (530_000, 5), (1_050_000, 9)])
+                                 (525_000, 17), (530_000, 5), (1_050_000, 9), (200_000, 33), (200_003, 65),
+                                 (733_330, 40), (600_001, 100)])
 def test_single_vector_units(dev, d, m):
     from paper_2107_03356_amd import Window
     say("single-vector units d =", d, "m =", m)
