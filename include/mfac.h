@@ -141,7 +141,9 @@ mfac_status mfac_window_replace(mfac_window w, int32_t slot, const float* g_new,
  * replacement. One read of the window per step instead of two for m <= 2048;
  * larger m runs the two passes per step of mfac_window_replace. Results equal
  * those of the separate calls up to the order of fp64 sums in the Gram
- * column. Not for an optimizer loop, whose next gradient depends on this
+ * column, and for a window small enough for the one-launch step of
+ * mfac_window_replace (ceil(d / 2048) <= 16, m * ceil(d / 2048) <= 32) in the other
+ * fp64 sums too. Not for an optimizer loop, whose next gradient depends on this
  * step's output. n >= 1; Gn and Yn must not alias each other or the window
  * storage. The ring head and step count advance by n. */
 mfac_status mfac_window_replace_seq(mfac_window w, int32_t n, const float* Gn, float* Yn);
@@ -201,7 +203,10 @@ mfac_status mfac_window_set_stream(mfac_window w, hipStream_t stream);
  * 0 stops (recorded events are kept until read). In mfac_window_replace_seq
  * phase 2 is the fused pass (G^T c of one step with G x of the next) for all
  * but the last step, and phase 0 runs once, for the first gradient. Each
- * recorded event costs a few microseconds of queue time between launches. */
+ * recorded event costs a few microseconds of queue time between launches. A
+ * replace of a small window (see mfac_window_replace_seq) runs as one launch
+ * without phases when not traced, and as the separate kernels when traced: the
+ * phase times are those of the latter. */
 #define MFAC_NPHASES 4
 mfac_status mfac_window_trace(mfac_window w, int32_t enable);
 
@@ -248,10 +253,12 @@ mfac_status mfac_static_precompute(mfac_static* out, int64_t d, int32_t block, i
 #define MFAC_STATIC_TRACE 1u /* record HIP events around the precompute's stages and
                                 mfac_obs_mask; read with mfac_static_trace_read */
 /* Fast mode (mfac_static_precompute only; m <= 4096, block <= 65536): the
- * Gram matrices, their Cholesky factors and inverses, and W in fp32 (products
- * and sums; large products as exact bf16 parts on the matrix cores: a Gram entry over at most 2048 columns,
- * wider blocks adding their 2048-column splits in fp64; W over the m rows;
- * the squares of W summed in fp64 for the diagonal). The inverse diagonal then
+ * Gram matrices, their Cholesky factors and inverses, and W in fp32 (values
+ * and sums; a product of two values, in the large matrix products, as the six
+ * largest of the nine products of their three bf16 parts, which leaves out at
+ * most 2^-26 of it). A Gram entry is summed over at most 2048 columns,
+ * wider blocks adding their 2048-column splits in fp64, W over the m rows,
+ * the squares of W in fp64 for the diagonal. The inverse diagonal then
  * carries the fp32 rounding (on gradient-like data with a well-conditioned
  * G_b G_b^T + m*lambda*I, a largest entry error of 4.1e-6 relative measured
  * at d = 4.19M, B = 2048, m = 1024). G is left intact: W and the fp32

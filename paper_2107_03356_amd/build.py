@@ -50,8 +50,10 @@ def build(verbose: bool = False) -> str:
         # report kernels that use per-lane scratch: a staging array the
         # compiler did not keep in registers is a performance bug; the few
         # spills of the MFMA tile kernels under their 4-waves-per-SIMD launch
-        # bounds (k_gram_window, k_gram_blocks, k_trmm_diag, k_bgemm with a
-        # transposed B) are measured wins over fewer waves without them
+        # bounds (k_gram_window, k_gram_blocks, fp64 k_bgemm with a transposed
+        # B) are measured wins over fewer waves without them; k_trmm32 (12 and
+        # 76 bytes) keeps a few values there that it reloads once per row
+        # tile, outside its k loop
         name = None
         for line in r.stderr.splitlines():
             m = re.search(r"Function Name: (\S+)", line)

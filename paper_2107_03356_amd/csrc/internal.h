@@ -154,8 +154,9 @@ hipError_t launch_scores(const float* theta, const double* diag, int64_t d, doub
                          int* err, hipStream_t st);
 // Radix selection of the keep-th largest score and the keep-mask
 struct SelectScratch {
-    unsigned int* hist;       // 256 bins
-    unsigned long long* state;  // prefix, mask, remaining rank, (unused)
+    unsigned int* hist;         // 2048 bins for each of the six digits
+    unsigned long long* state;  // 0: the selected key, 2: how many equal to it are kept, 3: whether that is all
+                                // of them; 4 + 2p, 5 + 2p: prefix and rank that pass p starts from
     unsigned int* chunk_cnt;  // per-chunk tie counts
     int nchunk;
 };
