@@ -189,7 +189,7 @@ def _pool_size():
 def test_static_pruning_full_size_setup(dev):
     """Draw G and theta on the GPU, keep the oracle's host copy, run the
     library's precompute + inverse diagonal + scores + mask: first in the fast
-    mode (fp32 matrix cores, G left intact), then in the fp64 mode (which
+    mode (fp32, G left intact), then in the fp64 mode (which
     writes W over G)."""
     from paper_2107_03356_amd import StaticBlocks
     wl = get_workload("static_d4.19m_b2048_m1024")
